@@ -1,24 +1,30 @@
 // Global top-B selection (Sec. 5.2 last paragraph, Algorithm 1 phase 3) and
 // the retained-row plan of eq. problem, one workgroup per (sequence, head).
 //
-// Scores map to order-preserving uint32 keys (NaN -> -inf, -0 -> +0). An
-// MSB-first radix select finds the key tau of the B-th largest prunable
-// score and how many tokens equal to tau must be kept; it starts below the
-// bits that every candidate shares (from the block's key min and max, or from
-// a lower bound for tau and the max) and takes 11-bit digits, so scores
-// spanning a few binades need up to three passes. The
-// write-out walks positions in order: tokens above tau are kept, tokens equal
-// to tau are kept while their rank among equals is below that count (lower
-// positions first), protected tokens are always kept. Histogram increments are
-// aggregated per wave with ballots (scores cluster by step utility, so most
-// lanes of a wave share a digit) before the LDS atomics.
+// Scores map to order-preserving uint32 keys (NaN -> -inf, -0 -> +0). A radix
+// search finds the key tau of the B-th largest prunable score and how many
+// tokens equal to tau must be kept. It counts 2048 equal bins between a lower
+// bound for tau and the largest key, then searches the bin that holds the
+// B-th key: that bin's few keys are gathered into LDS, and ballots rank up to
+// 64 of them at once. The write-out walks positions in order: tokens above tau
+// are kept, tokens equal to tau are kept while their rank among equals is below
+// that count (lower positions first), protected tokens are always kept.
 //
-// Sequences of up to 32768 tokens keep their keys in registers (32 per
-// thread, position tid + 1024 j in slot j); longer ones re-read the scores
-// in every pass. In a batch of 2 to 64 sequences the workgroups take the
-// rows of the longest sequences first. The work per key is plain VALU arithmetic over lane data;
-// per-slot lane masks are made where they are used, never held across a
-// phase, since 32 of them do not fit the scalar registers.
+// A thread holds runs of four consecutive positions (4 tid + 4096 b in block
+// b): one 16-byte load of scores and one 4-byte load of protected flags per
+// run. Rows of up to 65536 tokens keep their keys in registers, in code
+// for 1, 2, 4, 8 or 16 blocks chosen by the row's own length; longer rows are
+// read again in every phase, 8 blocks at a time. In a batch of 2 to 64
+// sequences the workgroups take the rows of the longest sequences first.
+//
+// What bounds it: vector issue on the one CU that holds a row and, for few or
+// short rows, the chain of loads, barriers and LDS round trips; so scans and
+// reductions run on DPP, a phase takes one or two barriers, and ties that are
+// all kept take a cheaper write-out. Times of stepkv_select, before (one
+// position per slot of 1024, up to three radix passes over all keys) and now:
+// 256 rows of 32768 tokens 21.4 -> 12.7 us, one such row 17.5 -> 10.9, 256 rows
+// of 16384 21.7 -> 10.5, 16 sequences of 4k to 32k tokens x 112 heads
+// 163 -> 81, 8 rows of 60000 136 -> 21, 64 rows of 131071 360 -> 70.
 #include "common.h"
 #include "internal.h"
 
@@ -27,16 +33,11 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kCached = 32;  // keys held in registers when N_s <= 32768
+constexpr int kBlock = 4 * kThreads;  // positions of one block: four per thread
+constexpr int kCachedBlocks = 16;     // blocks held in registers (rows of up to 65536 tokens)
+constexpr int kStreamBlocks = 8;      // blocks per pass over a longer row
 
-__device__ __forceinline__ uint32_t order_key(float p) {
-  uint32_t u = __float_as_uint(p);
-  u = (u & 0x7FFFFFFFu) > 0x7F800000u ? 0xFF800000u : u;  // NaN ranks as -inf
-  u = u == 0x80000000u ? 0u : u;                           // -0 ranks as +0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);       // never 0 for canonical values
-}
-
-// In registers, a protected token holds this key: above every score's key
+// A protected token holds this key: above every score's key
 // (+inf maps to 0xFF800000), so it is kept by the same test as a score above
 // tau; positions past the sequence hold 0. Neither is a candidate.
 constexpr uint32_t kProtKey = 0xFFFFFFFFu;
@@ -45,48 +46,58 @@ constexpr uint32_t kNoKey = 1u;
 
 constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
+constexpr int kList = 1024;  // keys of one bin that the search takes into LDS
+static_assert(kBins == 2 * kThreads, "each thread owns two bins");
 
-// Add one to h[bin] for every active lane: when every active lane of the wave
-// holds the same bin (scores cluster by step), one atomic adds the count;
-// otherwise each active lane adds one.
-__device__ __forceinline__ void wave_hist_add(uint32_t* h, bool active, uint32_t bin, int lane) {
-  const uint64_t act = ballot(active);
-  if (!act) return;
-  const int leader = __builtin_ctzll(act);
-  const uint32_t lb = __builtin_amdgcn_readlane(bin, leader);
-  const uint64_t same = ballot(active && bin == lb);
-  if (same == act) {
-    if (lane == leader) atomicAdd(&h[lb], (uint32_t)__popcll(act));
-  } else if (active) {
-    atomicAdd(&h[bin], 1u);
-  }
+// Inclusive prefix sum over the wave in lane order (DPP row shifts, then the
+// row totals broadcast to the rows above: no LDS round trip).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
 }
 
-__device__ __forceinline__ int block_sum_int(int v, int* scratch) {
-  v = wave_sum_int(v);
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int t = 0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += scratch[w];
-  __syncthreads();
-  return t;
+// Maximum (MAX) or minimum over the wave, in every lane.
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
+  auto pick = [](uint32_t a, int b) { return MAX ? max(a, (uint32_t)b) : min(a, (uint32_t)b); };
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));
+  v = pick(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Exclusive prefix sum over the workgroup in thread order (modulo 2^32).
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* scratch) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t inc = v;
+// The median of three (v_med3_u32).
+__device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c) {
+  return max(min(a, b), min(max(a, b), c));
+}
+
+// Lanes of one bin from which a wave adds to the histogram by groups: LDS
+// atomics of many lanes on one word run one after another (256 rows of 32768
+// scores with a handful of distinct values: 80 us without the groups, 30 with).
+constexpr int kClustered = 16;
+
+// Add one to h[bin] for every active lane, the first two distinct bins with one
+// atomic each.
+__device__ __forceinline__ void hist_add_grouped(uint32_t* h, bool active, uint32_t bin, int lane) {
+  uint64_t rest = ballot(active);
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t x = (uint32_t)__shfl_up((int)inc, o, kWave);
-    if (lane >= o) inc += x;
+  for (int g = 0; g < 2; ++g) {
+    if (rest == 0ull) return;
+    const int leader = __builtin_ctzll(rest);
+    const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
+    const uint64_t same = ballot(bin == lb) & rest;
+    if (lane == leader) atomicAdd(&h[lb], (uint32_t)__popcll(same));
+    rest &= ~same;
   }
-  if (lane == 63) scratch[wave] = inc;
-  __syncthreads();
-  uint32_t before = 0u;
-  for (int w = 0; w < wave; ++w) before += scratch[w];
-  __syncthreads();
-  return before + inc - v;
+  if ((rest >> lane) & 1ull) atomicAdd(&h[bin], 1u);
 }
 
 // Kept candidates of one slot grouped by step: one atomic per step per wave.
@@ -100,105 +111,6 @@ __device__ __forceinline__ void count_kept_steps(int32_t* kept, int nsteps, int 
     if (lane == leader) atomicAdd(&kept[kk], (int)__popcll(grp));
     pend &= ~grp;
   }
-}
-
-// Candidate count and key range over the workgroup in one barrier round.
-// hist[0..kBins) is cleared before the same barrier for the first pass.
-__device__ __forceinline__ void reduce_count_range(int& npr, uint32_t& kmin, uint32_t& kmax,
-                                                   uint32_t (*red)[kWaves], uint32_t* hist) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int e = threadIdx.x; e < kBins; e += kThreads) hist[e] = 0u;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-  }
-  if (lane == 0) {
-    red[0][wave] = (uint32_t)npr;
-    red[1][wave] = kmin;
-    red[2][wave] = kmax;
-  }
-  __syncthreads();
-  npr = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    npr += (int)red[0][w];
-    kmin = min(kmin, red[1][w]);
-    kmax = max(kmax, red[2][w]);
-  }
-}
-
-// MSB-first radix search for the key tau of the ktake-th largest candidate
-// (kmin..kmax: candidate key range, kmin < kmax) and the number `need` of
-// tokens equal to tau that are kept. count(h, pmask, prefix, shift, nbins)
-// adds each candidate key with (key & pmask) == prefix to bin
-// (key >> shift) & (nbins - 1) of h. Two histograms alternate: each pass
-// counts into one and clears the other, which only the previous pass read;
-// the first must be clear and visible on entry.
-template <typename Count>
-__device__ __forceinline__ void radix_search(uint32_t kmin, uint32_t kmax, int ktake,
-                                             uint32_t* hist, int* sh, Count count, uint32_t& tau,
-                                             int& need) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int lo = 32 - __builtin_clz(kmin ^ kmax);  // undecided low bits
-  const uint32_t low = lo == 32 ? 0xFFFFFFFFu : ((1u << lo) - 1u);
-  uint32_t pmask = ~low;
-  uint32_t prefix = kmax & pmask;
-  int krem = ktake;
-  int buf = 0;
-  while (lo > 0) {
-    const int width = min(kDigitBits, lo);
-    const int shift = lo - width;
-    const int nbins = 1 << width;
-    uint32_t* h = hist + buf * kBins;
-    uint32_t* hn = hist + (buf ^ 1) * kBins;
-    for (int e = tid; e < kBins; e += kThreads) hn[e] = 0u;
-    count(h, pmask, prefix, shift, nbins);
-    __syncthreads();
-    if (wave == 0) {
-      // lane owns bins 32*lane .. 32*lane+31 (bins >= nbins stay zero);
-      // find the bin holding the krem-th largest key
-      constexpr int kPer = kBins / kWave;
-      int b0 = kPer * lane;
-      asm volatile("" : "+v"(b0));  // bin numbers made here, not held across passes
-      const uint4* hp = reinterpret_cast<const uint4*>(h + b0);
-      uint32_t own = 0u;
-#pragma unroll
-      for (int q = 0; q < kPer / 4; ++q) {
-        const uint4 h4 = hp[q];
-        own += (h4.x + h4.y) + (h4.z + h4.w);
-      }
-      uint32_t suf = own;  // inclusive suffix over lanes >= lane
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t x = __shfl_down(suf, o, kWave);
-        if (lane + o < 64) suf += x;
-      }
-      uint32_t above = suf - own;  // keys in bins owned by higher lanes
-      auto visit = [&](uint32_t c, int bin) {
-        if (above < (uint32_t)krem && (uint32_t)krem <= above + c) {
-          sh[0] = bin;
-          sh[1] = krem - (int)above;
-        }
-        above += c;
-      };
-#pragma unroll
-      for (int q = kPer / 4 - 1; q >= 0; --q) {  // bins from high to low
-        const uint4 h4 = hp[q];
-        visit(h4.w, b0 + 4 * q + 3);
-        visit(h4.z, b0 + 4 * q + 2);
-        visit(h4.y, b0 + 4 * q + 1);
-        visit(h4.x, b0 + 4 * q);
-      }
-    }
-    __syncthreads();
-    prefix |= (uint32_t)sh[0] << shift;
-    pmask |= (uint32_t)(nbins - 1) << shift;
-    krem = sh[1];
-    lo = shift;
-    buf ^= 1;
-  }
-  tau = prefix;
-  need = krem;  // tokens equal to tau that are kept, lowest positions first
 }
 
 struct RowSetup {
@@ -249,18 +161,23 @@ __device__ __forceinline__ RowSetup row_setup(const SelectArgs& a) {
   return r;
 }
 
-// Protected tokens of sequence s, counted by the whole workgroup: 16 at a
-// time from aligned 16-byte words, the unaligned head and tail one byte at a
-// time.
-__device__ int count_protected(const SelectArgs& a, int s, int* scratch) {
+__device__ __forceinline__ int budget_of(const SelectArgs& a, int s) {
+  return a.budgets ? max(1, a.budgets[s]) : a.budget;
+}
+
+// Protected tokens of sequence s, counted by one wave: 16 at a time from
+// aligned 16-byte words, the unaligned head and tail one byte at a time.
+__device__ __forceinline__ int count_protected(const SelectArgs& a, int s) {
+  const int lane = threadIdx.x & 63;
   const int seq0 = a.cu_seqlens[s], ns = a.cu_seqlens[s + 1] - seq0;
   const int misal = (int)(reinterpret_cast<uintptr_t>(a.prot + seq0) & 15);
   const int head = min(ns, (16 - misal) & 15);
   const int nvec = (ns - head) / 16;
   int np = 0;
-  if ((int)threadIdx.x < head) np += a.prot[seq0 + threadIdx.x] != 0;
+  if (lane < head) np += a.prot[seq0 + lane] != 0;
   const uint4* vp = reinterpret_cast<const uint4*>(a.prot + seq0 + head);
-  for (int i = threadIdx.x; i < nvec; i += kThreads) {
+#pragma unroll 4
+  for (int i = lane; i < nvec; i += kWave) {
     const uint4 w = vp[i];
     const uint32_t x[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
@@ -271,43 +188,44 @@ __device__ int count_protected(const SelectArgs& a, int s, int* scratch) {
       np += __builtin_popcount(b & 0x01010101u);
     }
   }
-  for (int i = head + 16 * nvec + threadIdx.x; i < ns; i += kThreads) np += a.prot[seq0 + i] != 0;
-  return block_sum_int(np, scratch);
+  for (int i = head + 16 * nvec + lane; i < ns; i += kWave) np += a.prot[seq0 + i] != 0;
+  return __builtin_amdgcn_readlane((int)wave_scan((uint32_t)np), 63);
 }
 
-__device__ __forceinline__ int budget_of(const SelectArgs& a, int s) {
-  return a.budgets ? max(1, a.budgets[s]) : a.budget;
+// Retained rows of the sequences t0 <= t < t1, t = t0 + wave + 16 k per wave
+// (cu_retained[s+1] - cu_retained[s] = n_protected_s + min(B_s, N_s - n_protected_s)),
+// summed over the workgroup. Block-uniform call.
+__device__ __forceinline__ int retained_between(const SelectArgs& a, int t0, int t1, uint32_t* scratch) {
+  const int wave = uniform(threadIdx.x >> 6);
+  int acc = 0;
+  for (int t = t0 + wave; t < t1; t += kWaves) {
+    const int nt = a.cu_seqlens[t + 1] - a.cu_seqlens[t];
+    const int np = count_protected(a, t);
+    acc += np + min(budget_of(a, t), nt - np);
+  }
+  if ((threadIdx.x & 63) == 0) scratch[wave] = (uint32_t)acc;
+  __syncthreads();
+  int sum = 0;
+  for (int w = 0; w < kWaves; ++w) sum += (int)scratch[w];
+  __syncthreads();
+  return sum;
 }
 
-// cu_retained[s+1] - cu_retained[s] = n_protected_s + min(B_s, N_s - n_protected_s)
 // Without heads there are no selection workgroups; one workgroup writes the plan.
 __global__ __launch_bounds__(kThreads) void retained_plan_kernel(SelectArgs a) {
-  __shared__ int scratch[kWaves];
+  __shared__ uint32_t scratch[kWaves];
   int acc = 0;
   if (threadIdx.x == 0) a.cu_retained[0] = 0;
   for (int s = 0; s < a.S; ++s) {
-    const int ns = a.cu_seqlens[s + 1] - a.cu_seqlens[s];
-    const int np = count_protected(a, s, scratch);
-    acc += np + min(budget_of(a, s), ns - np);
+    acc += retained_between(a, s, s + 1, scratch);
     if (threadIdx.x == 0) a.cu_retained[s + 1] = acc;
   }
 }
 
 // The same plan from the selection workgroups of head 0: the workgroup of
-// sequence s counts the protected tokens of the sequences before it (none
-// with a single sequence) before it loads its keys, and adds its own
-// sequence once its candidate count npr = N_s - n_protected_s is known.
-// Block-uniform: only the head-0 workgroups call these.
-__device__ int retained_before(const SelectArgs& a, int s, int* scratch) {
-  int acc = 0;
-  for (int t = 0; t < s; ++t) {
-    const int nt = a.cu_seqlens[t + 1] - a.cu_seqlens[t];
-    const int np = count_protected(a, t, scratch);
-    acc += np + min(budget_of(a, t), nt - np);
-  }
-  return acc;
-}
-
+// sequence s counts the protected tokens of the sequences before it, one
+// sequence per wave (none with a single sequence), and adds its own sequence
+// once its candidate count npr = N_s - n_protected_s is known.
 __device__ __forceinline__ void write_retained(const SelectArgs& a, int s, int before, int ns,
                                                int npr, int B) {
   if (threadIdx.x == 0) {
@@ -316,291 +234,462 @@ __device__ __forceinline__ void write_retained(const SelectArgs& a, int s, int b
   }
 }
 
-// The M-th largest candidate key among a thread's slots, 0 when it holds
-// fewer than M candidates (candidate keys are never 0).
-template <int M>
-__device__ __forceinline__ uint32_t mth_largest(const uint32_t (&keys)[kCached]) {
-  uint32_t top[M];  // the largest so far, in descending order
-#pragma unroll
-  for (int q = 0; q < M; ++q) top[q] = 0u;
-#pragma unroll
-  for (int j = 0; j < kCached; ++j) {
-    uint32_t x = keys[j] - 1u < kProtKey - 1u ? keys[j] : 0u;
-#pragma unroll
-    for (int q = 0; q < M; ++q) {
-      const uint32_t hi = max(top[q], x);
-      x = min(top[q], x);
-      top[q] = hi;
-    }
-  }
-  return top[M - 1];
-}
+struct Scratch {
+  uint32_t hist[kBins];  // bins of the search; clear on entry to every count
+  uint32_t list[kList];  // the keys of the bin searched last
+  uint32_t cnt[kCachedBlocks * kWaves];  // write-out: per (block, wave) sure | ties << 16
+  uint32_t red[4][kWaves];
+  uint32_t wtot[kWaves];
+  uint32_t found[3];  // bin, rank within it, keys in it
+  uint32_t nlist;
+};
 
-// ---------------------------------------------------------------- N_s <= 32768
-__global__ __launch_bounds__(kThreads) void select_cached_kernel(SelectArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[2 * kBins];
-  __shared__ uint32_t red[5][kWaves];
-  __shared__ int sh[2];
-  __shared__ int plan_scratch[kWaves];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const RowSetup r = row_setup(a);
-  const int ns = r.ns;
-  const float* __restrict__ P = a.scores + (size_t)r.lh * a.ntot + r.seq0;
-  const uint8_t* __restrict__ prot = a.prot + r.seq0;
-  const int plan_before = r.lh == 0 ? retained_before(a, r.s, plan_scratch) : 0;
-
-  // every load issued before any is used: indices clamped into the sequence
-  float pv[kCached];
-  uint32_t pb[kCached];
-  if (ns > 0) {
+// Keys of NB blocks from P and prot (at the first block's base), whose first
+// `rem` positions exist: keys[4 b + e] is position 4096 b + 4 tid + e. Every
+// load of 4 blocks is issued before any is used (8 took 0.4 us more on a row of
+// 32768 tokens); whole blocks take one 16-byte and one 4-byte load per thread
+// (any alignment of P and prot).
+template <int NB>
+__device__ __forceinline__ void load_keys(const float* __restrict__ P,
+                                          const uint8_t* __restrict__ prot, int rem,
+                                          uint32_t* keys) {
+  if constexpr (NB > 4) {
+    load_keys<4>(P, prot, rem, keys);
 #pragma unroll
-    for (int j = 0; j < kCached; ++j) {
-      const int ic = min(tid + kThreads * j, ns - 1);
-      pv[j] = P[ic];
-      pb[j] = prot[ic];
-    }
+    for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(keys[j]));
+    load_keys<NB - 4>(P + 4 * kBlock, prot + 4 * kBlock, rem - 4 * kBlock, keys + 16);
+    return;
   }
-  uint32_t keys[kCached];
-  int npr = 0;  // wave total
-  uint32_t kmin1 = 0xFFFFFFFFu, kmax1 = 0u;  // candidate key - 1 and + 1
+  const int p4 = 4 * (int)threadIdx.x;
+  float pv[4 * NB];
+  uint32_t pw[NB];
 #pragma unroll
-  for (int j = 0; j < kCached; ++j) {
-    // NaN -> -inf and -0 -> +0 in float arithmetic, then the sign flip
-    const float q = fmaxf(pv[j], -INFINITY) + 0.0f;
-    const uint32_t u = __float_as_uint(q);
-    const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-    const bool in = tid + kThreads * j < ns;
-    keys[j] = in ? (pb[j] == 0u ? key : kProtKey) : 0u;
-    // key - 1 wraps 0 to the top and puts kProtKey just below it
-    const uint32_t km = keys[j] - 1u;
-    npr += __popcll(ballot(km < kProtKey - 1u));
-    kmin1 = min(kmin1, km);
-    kmax1 = max(kmax1, keys[j] + 1u);  // kProtKey + 1 wraps to 0
-  }
-  // A lower bound for tau: each thread holding at least m candidates has m
-  // of them at or above its m-th largest, so at least m times as many
-  // candidates as there are such threads lie at or above the smallest of
-  // those m-th largest keys; when ktake is within that number, tau lies there
-  // too and the search skips every key below it. m = 1, 2 or 4, the least
-  // for which the budget can be within the bound.
-  const int m = r.B <= kThreads ? 1 : (r.B <= 2 * kThreads ? 2 : 4);
-  uint32_t mth;  // this thread's m-th largest candidate key, 0 with fewer than m
-  if (m == 1) {
-    mth = kmax1 >= 2u ? kmax1 - 1u : 0u;
-  } else {
-    mth = m == 2 ? mth_largest<2>(keys) : mth_largest<4>(keys);
-  }
-  const bool has = mth != 0u;
-  uint32_t tmax = has ? mth : 0xFFFFFFFFu;
-  const int nthr = __popcll(ballot(has));  // wave total
-  // count, key range and the bound, reduced in one barrier round; kmin1 and
-  // kmax1 in the shifted domains, where non-candidates lose every min and max
-  for (int e = tid; e < kBins; e += kThreads) hist[e] = 0u;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmin1 = min(kmin1, (uint32_t)__shfl_xor((int)kmin1, o, kWave));
-    kmax1 = max(kmax1, (uint32_t)__shfl_xor((int)kmax1, o, kWave));
-    tmax = min(tmax, (uint32_t)__shfl_xor((int)tmax, o, kWave));
-  }
-  if (lane == 0) {
-    red[0][wave] = (uint32_t)npr;
-    red[1][wave] = kmin1;
-    red[2][wave] = kmax1;
-    red[3][wave] = tmax;
-    red[4][wave] = (uint32_t)nthr;
-  }
-  __syncthreads();
-  npr = 0;
-  int nthr_all = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    npr += (int)red[0][w];
-    kmin1 = min(kmin1, red[1][w]);
-    kmax1 = max(kmax1, red[2][w]);
-    tmax = min(tmax, red[3][w]);
-    nthr_all += (int)red[4][w];
-  }
-  const uint32_t kmin = kmin1 + 1u, kmax = kmax1 - 1u;  // used only when there are candidates
-  const int ktake = min(r.B, npr);
-  const bool take_all = ktake == npr;
-  if (r.lh == 0) write_retained(a, r.s, plan_before, ns, npr, r.B);
-
-  uint32_t tau = 0u;
-  int need = 0;
-  if (!take_all) {
-    const uint32_t lbound = ktake <= m * nthr_all ? tmax : kmin;  // tau >= lbound
-    if (lbound == kmax) {
-      tau = kmax;  // every candidate from the bound up ties
-      need = ktake;
+  for (int b = 0; b < NB; ++b) {
+    const int left = rem - kBlock * b;  // uniform
+    pw[b] = 0u;
+    if (left >= kBlock) {
+      __builtin_memcpy(&pv[4 * b], P + kBlock * b + p4, 16);
+      __builtin_memcpy(&pw[b], prot + kBlock * b + p4, 4);
     } else {
-      const uint32_t span = kmax - lbound;
-      auto count = [&](uint32_t* h, uint32_t pmask, uint32_t prefix, int shift, int nbins) {
-        // fresh compares in every pass rather than lane masks held across passes
 #pragma unroll
-        for (int j = 0; j < kCached; ++j) asm volatile("" : "+v"(keys[j]));
-        const uint32_t dm = (uint32_t)(nbins - 1);
-        // keys in [lbound, kmax] only: 0 and kProtKey fall outside
+      for (int e = 0; e < 4; ++e) pv[4 * b + e] = 0.f;
+      if (left > 0) {
 #pragma unroll
-        for (int j = 0; j < kCached; ++j)
-          wave_hist_add(h, keys[j] - lbound <= span && (keys[j] & pmask) == prefix,
-                        (keys[j] >> shift) & dm, lane);
-      };
-      radix_search(lbound, kmax, ktake, hist, sh, count, tau, need);
-    }
-  }
-
-  // ---- ordered write-out. Ranks in position order straight from the
-  // strided slots: per (slot, wave) the numbers of sure keeps and of ties,
-  // one exclusive scan over the 512 (slot, wave) pairs, which are already in
-  // position order, and ballots for the ranks inside a wave. A tie is kept
-  // when fewer than `need` ties precede it, so the tokens kept before
-  // position p are the sure keeps before p plus min(ties before p, need).
-  int32_t* __restrict__ out = a.idx + (size_t)r.lh * a.ntot + r.seq0;
-  const uint32_t t_sure = take_all ? 0u : tau;    // key > t_sure: kept for sure
-  const uint32_t t_tie = take_all ? kNoKey : tau;  // key == t_tie: a tie
-  uint32_t* cnt = hist;  // [kCached][kWaves]: sure | ties << 16
-#pragma unroll
-  for (int j = 0; j < kCached; ++j) asm volatile("" : "+v"(keys[j]));
-#pragma unroll
-  for (int j = 0; j < kCached; ++j) {
-    const uint32_t c = (uint32_t)__popcll(ballot(keys[j] > t_sure)) |
-                       ((uint32_t)__popcll(ballot(keys[j] == t_tie)) << 16);
-    if (lane == 0) cnt[j * kWaves + wave] = c;
-  }
-  __syncthreads();
-  // at most 32768 tokens: both halves of the packed sums stay below 2^16
-  const uint32_t ex = block_exclusive_scan(tid < kCached * kWaves ? cnt[tid] : 0u, red[0]);
-  if (tid < kCached * kWaves) cnt[tid] = ex;
-  __syncthreads();
-  const uint32_t base_lane = lane < kCached ? cnt[lane * kWaves + wave] : 0u;
-#pragma unroll
-  for (int j = 0; j < kCached; ++j) asm volatile("" : "+v"(keys[j]));
-  const int32_t* __restrict__ sid = a.step_ids + r.seq0;
-  int tid_w = tid;
-  asm volatile("" : "+v"(tid_w));  // positions and addresses made here, not carried from the top
-#pragma unroll
-  for (int j = 0; j < kCached; ++j) {
-    const bool sure = keys[j] > t_sure, tie = keys[j] == t_tie;
-    const uint64_t bs = ballot(sure), bt = ballot(tie);
-    if ((bs | bt) == 0ull) continue;
-    const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)base_lane, j);
-    const int s_before = (int)(base & 0xFFFFu) + lanes_below(bs);
-    const int t_before = (int)(base >> 16) + lanes_below(bt);
-    const bool keep = sure || (tie && t_before < need);
-    const int i = tid_w + kThreads * j;
-    if (keep) out[s_before + min(t_before, need)] = i;
-    if (r.kept) {
-      const bool cand = keys[j] - 1u < kProtKey - 1u;
-      count_kept_steps(r.kept, r.nsteps, (keep && cand) ? sid[i] : -1, lane);
-    }
-  }
-}
-
-// ---------------------------------------------------------------- N_s > 32768
-// Keys are re-read from the scores in every pass; the write-out ranks one
-// slot at a time with two barrier rounds per slot.
-__global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[2 * kBins];
-  __shared__ uint32_t red[3][kWaves];
-  __shared__ int wcnt[2][2][kWaves];
-  __shared__ int sh[2];
-  __shared__ int plan_scratch[kWaves];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const RowSetup r = row_setup(a);
-  const int ns = r.ns;
-  const float* __restrict__ P = a.scores + (size_t)r.lh * a.ntot + r.seq0;
-  const uint8_t* __restrict__ prot = a.prot + r.seq0;
-  const int plan_before = r.lh == 0 ? retained_before(a, r.s, plan_scratch) : 0;
-  // position of slot j of this thread: tid + kThreads * j (coalesced)
-  auto key_at = [&](int j) -> uint32_t {
-    const int i = tid + kThreads * j;
-    if (i >= ns || prot[i] != 0) return 0u;
-    return order_key(P[i]);
-  };
-  const int nslots = (ns + kThreads - 1) / kThreads;
-  int npr = 0;
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  for (int j = 0; j < nslots; ++j) {
-    const uint32_t key = key_at(j);
-    npr += key != 0u ? 1 : 0;
-    kmin = min(kmin, key != 0u ? key : 0xFFFFFFFFu);
-    kmax = max(kmax, key);
-  }
-  npr = wave_sum_int(npr);
-  reduce_count_range(npr, kmin, kmax, red, hist);
-  const int ktake = min(r.B, npr);
-  const bool take_all = ktake == npr;
-  if (r.lh == 0) write_retained(a, r.s, plan_before, ns, npr, r.B);
-
-  uint32_t tau = 0u;
-  int need = 0;
-  if (!take_all) {
-    if (kmin == kmax) {
-      tau = kmin;
-      need = ktake;
-    } else {
-      auto count = [&](uint32_t* h, uint32_t pmask, uint32_t prefix, int shift, int nbins) {
-        for (int j = 0; j < nslots; ++j) {
-          const uint32_t key = key_at(j);
-          wave_hist_add(h, key != 0u && (key & pmask) == prefix,
-                        (key >> shift) & (uint32_t)(nbins - 1), lane);
+        for (int e = 0; e < 4; ++e) {
+          const int i = kBlock * b + min(p4 + e, left - 1);
+          pv[4 * b + e] = P[i];
+          pw[b] |= (uint32_t)prot[i] << (8 * e);
         }
-      };
-      radix_search(kmin, kmax, ktake, hist, sh, count, tau, need);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int left = rem - kBlock * b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // NaN -> -inf and -0 -> +0 in float arithmetic, then the sign flip
+      const float q = fmaxf(pv[4 * b + e], -INFINITY) + 0.0f;
+      const uint32_t u = __float_as_uint(q);
+      const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+      keys[4 * b + e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? key : kProtKey;
+    }
+    if (left < kBlock) {  // uniform: positions past the sequence
+#pragma unroll
+      for (int e = 0; e < 4; ++e) keys[4 * b + e] = p4 + e < left ? keys[4 * b + e] : 0u;
+    }
+  }
+}
+
+// One (sequence, head) row of ns tokens. STREAM: the keys are read again in
+// every phase, kStreamBlocks blocks at a time; otherwise NB blocks hold the row.
+template <int NB, bool STREAM>
+struct Row {
+  static constexpr int NK = 4 * NB;
+  using Keys = uint32_t[NK];
+  Scratch& sh;
+  const float* __restrict__ P;
+  const uint8_t* __restrict__ prot;
+  const int32_t* __restrict__ sid;
+  int32_t* __restrict__ out;
+  int32_t* __restrict__ kept;  // or null
+  int ns, nsteps;
+
+  // f(segment) over the row's segments of NB blocks with their keys in `keys`
+  template <typename F>
+  __device__ __forceinline__ void each(Keys& keys, F&& f) const {
+    if constexpr (STREAM) {
+      const int nseg = (ns - 1) / (kBlock * NB) + 1;
+      for (int sg = 0; sg < nseg; ++sg) {
+        load_keys<NB>(P + (size_t)sg * (kBlock * NB), prot + (size_t)sg * (kBlock * NB),
+                      ns - sg * (kBlock * NB), keys);
+        f(sg);
+      }
+    } else {
+      // fresh compares in every phase rather than lane masks held across phases
+#pragma unroll
+      for (int j = 0; j < NK; ++j) asm volatile("" : "+v"(keys[j]));
+      f(0);
     }
   }
 
-  int32_t* __restrict__ out = a.idx + (size_t)r.lh * a.ntot + r.seq0;
-  const int32_t* __restrict__ sid = a.step_ids + r.seq0;
-  int tie_base = 0, out_base = 0;
-  for (int j = 0; j < nslots; ++j) {
-    const uint32_t key = key_at(j);
-    const int par = j & 1;
-    const int i = tid + kThreads * j;
-    const bool valid = i < ns;
-    const bool cand = key != 0u;
-    const bool definite = (valid && prot[i] != 0) || (cand && (take_all || key > tau));
-    const bool tie = cand && !take_all && key == tau;
-    const uint64_t bt = ballot(tie);
-    if (lane == 0) wcnt[par][0][wave] = __popcll(bt);
-    __syncthreads();
-    int before = 0, total = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      const int c = wcnt[par][0][w];
-      before += w < wave ? c : 0;
-      total += c;
-    }
-    const bool keep = definite || (tie && tie_base + before + lanes_below(bt) < need);
-    tie_base += total;
-    const uint64_t bk = ballot(keep);
-    if (lane == 0) wcnt[par][1][wave] = __popcll(bk);
-    __syncthreads();
-    int kb = 0, kt = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      const int c = wcnt[par][1][w];
-      kb += w < wave ? c : 0;
-      kt += c;
-    }
-    if (keep) out[out_base + kb + lanes_below(bk)] = i;
-    out_base += kt;
-    if (r.kept) count_kept_steps(r.kept, r.nsteps, (keep && cand) ? sid[i] : -1, lane);
+  // Candidates (npr, of this wave), the largest candidate key + 1 and this
+  // thread's M-th largest key + 1 (0 or 1: fewer than M candidates). In the +1
+  // domain a protected token is 0 and a position past the sequence 1.
+  template <int M>
+  __device__ __forceinline__ void survey(Keys& keys, int& npr, uint32_t& kmax1, uint32_t& mth1) const {
+    uint32_t top[M];  // the largest so far, in descending order
+#pragma unroll
+    for (int q = 0; q < M; ++q) top[q] = 0u;
+    each(keys, [&](int) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        const uint32_t x = keys[j] + 1u;
+        npr += __popcll(ballot(x > 1u));
+#pragma unroll
+        for (int q = M - 1; q > 0; --q) top[q] = median(top[q - 1], top[q], x);
+        top[0] = max(top[0], x);
+      }
+    });
+    kmax1 = top[0];
+    mth1 = top[M - 1];
   }
+
+  // The bin holding the krem-th largest counted key (sh.hist, cleared while it
+  // is read): thread t owns bins kBins - 1 - 2t and kBins - 2 - 2t, so that the
+  // prefix in thread order counts the keys from the top.
+  __device__ __forceinline__ void find_bin(int krem) const {
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int b0 = kBins - 2 - 2 * tid;
+    uint2* hp = reinterpret_cast<uint2*>(&sh.hist[b0]);
+    const uint2 c = *hp;
+    *hp = make_uint2(0u, 0u);
+    const uint32_t own = c.x + c.y;
+    const uint32_t incl = wave_scan(own);
+    if (lane == 63) sh.wtot[wave] = incl;
+    __syncthreads();
+    const uint32_t tot = wave_scan(lane < kWaves ? sh.wtot[lane] : 0u);
+    const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)tot, wave - 1) : 0u;
+    const uint32_t above = before + incl - own, k = (uint32_t)krem;
+    if (above < k && k <= above + own) {
+      const bool hi = k <= above + c.y;
+      sh.found[0] = (uint32_t)(hi ? b0 + 1 : b0);
+      sh.found[1] = hi ? k - above : k - above - c.y;
+      sh.found[2] = hi ? c.y : c.x;
+      sh.nlist = 0u;
+    }
+    __syncthreads();
+  }
+
+  // The key tau of the krem-th largest of the candidates with keys in
+  // [lo, lo + span] (span > 0) and the number `need` of tokens equal to tau
+  // that are kept; need = 0 when every tie is kept, with tau then one below
+  // that key. sh.hist is clear and visible on entry.
+  __device__ __forceinline__ void search(Keys& keys, uint32_t lo, uint32_t span, int krem,
+                                         uint32_t& tau, int& need) const {
+    const int tid = threadIdx.x, lane = tid & 63;
+    int shift, n;
+    // the bin found last becomes the range; true when it is a single key
+    auto narrow = [&]() __attribute__((always_inline)) {
+      find_bin(krem);
+      lo += uniform((int)sh.found[0]) << shift;
+      krem = uniform((int)sh.found[1]);
+      n = uniform((int)sh.found[2]);
+      span = (1u << shift) - 1u;
+      tau = lo;
+      need = krem;
+      return shift == 0;
+    };
+    do {  // count the row's keys (again only while a bin holds more than kList)
+      shift = max(0, 32 - kDigitBits - __builtin_clz(span));
+      each(keys, [&](int) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {  // keys 0 and kProtKey fall outside
+          uint32_t d[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) d[e] = keys[4 * b + e] - lo;
+          const uint64_t act = ballot(d[0] <= span);
+          bool clustered = false;  // many lanes share the first lane's bin
+          if (act != 0ull) {
+            const uint32_t lead =
+                (uint32_t)__builtin_amdgcn_readlane((int)d[0], __builtin_ctzll(act)) >> shift;
+            clustered = __popcll(ballot(d[0] >> shift == lead)) >= kClustered;
+          }
+          if (clustered) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) hist_add_grouped(sh.hist, d[e] <= span, d[e] >> shift, lane);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (d[e] <= span) atomicAdd(&sh.hist[d[e] >> shift], 1u);
+          }
+        }
+      });
+      __syncthreads();
+      if (narrow()) return;
+    } while (n > kList);
+    each(keys, [&](int) __attribute__((always_inline)) {  // the bin's keys into LDS, in any order
+#pragma unroll
+      for (int j = 0; j < NK; ++j)
+        if (keys[j] - lo <= span) sh.list[atomicAdd(&sh.nlist, 1u)] = keys[j];
+    });
+    __syncthreads();
+    const int nlist = n;
+    while (n > kWave) {
+      shift = max(0, 32 - kDigitBits - __builtin_clz(span));
+      const uint32_t d = tid < nlist ? sh.list[tid] - lo : 0u;
+      if (tid < nlist && d <= span) atomicAdd(&sh.hist[d >> shift], 1u);
+      __syncthreads();
+      if (narrow()) return;
+      if (n <= kWave) {  // the list's keys in the bin, to its front
+        const uint32_t key = tid < nlist ? sh.list[tid] : 0u;
+        __syncthreads();
+        if (tid < nlist && key - lo <= span) sh.list[atomicAdd(&sh.nlist, 1u)] = key;
+        __syncthreads();
+      }
+    }
+    // rank the last keys: lane l holds key l, wave w ranks keys w, w + 16, ..
+    const int wave = uniform(tid >> 6);
+    const uint32_t mine = lane < n ? sh.list[lane] : 0u;  // 0: below every candidate
+    for (int i = wave; i < n; i += kWaves) {
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+      const int gt = __popcll(ballot(mine > o)), ge = __popcll(ballot(mine >= o));
+      if (gt < krem && krem <= ge && lane == 0) {  // equal keys write equal values
+        sh.found[0] = o;
+        sh.found[1] = (uint32_t)(krem - gt);
+        sh.found[2] = (uint32_t)(ge - gt);
+      }
+    }
+    __syncthreads();
+    tau = (uint32_t)uniform((int)sh.found[0]);
+    need = uniform((int)sh.found[1]);
+    if (need == uniform((int)sh.found[2])) {  // every tie is kept: all above tau - 1
+      --tau;
+      need = 0;
+    }
+  }
+
+  // Ordered write-out. Per (block, wave) the numbers of sure keeps and of ties
+  // go to LDS, in position order; every wave scans them and ranks its own
+  // tokens with ballots (a lane's four positions follow each other). A tie is
+  // kept when fewer than `need` ties precede it, so the tokens kept before
+  // position p are the sure keeps before p plus min(ties before p, need).
+  // Without TIES only keys above t_sure are kept.
+  template <bool TIES>
+  __device__ __forceinline__ void write_out(Keys& keys, uint32_t t_sure, int need) const {
+    const uint32_t t_tie = TIES ? t_sure : kNoKey;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    int sure0 = 0, tie0 = 0;  // sure keeps and ties of the segments before this one
+    each(keys, [&](int sg) __attribute__((always_inline)) {
+      uint32_t cw = 0u;  // lane b: block b of this wave
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        uint32_t cs = 0u, ct = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          cs += (uint32_t)__popcll(ballot(keys[4 * b + e] > t_sure));
+          if (TIES) ct += (uint32_t)__popcll(ballot(keys[4 * b + e] == t_tie));
+        }
+        uint32_t c = cs | (ct << 16);
+        asm volatile("" : "+s"(c));  // counted here, so that no ballot outlives its block
+        cw = lane == b ? c : cw;
+      }
+      if (STREAM) __syncthreads();  // the counts of the segment before this one are read
+      if (lane < NB) sh.cnt[lane * kWaves + wave] = cw;
+      __syncthreads();
+      // four (block, wave) pairs per lane, in position order
+      uint4 c4 = make_uint4(0u, 0u, 0u, 0u);
+      if (lane < 4 * NB) c4 = reinterpret_cast<const uint4*>(sh.cnt)[lane];
+      const uint32_t own = (c4.x + c4.y) + (c4.z + c4.w);
+      const uint32_t incl = wave_scan(own);
+      const int sub = wave & 3;  // this wave's pair of block b is the sub-th of lane 4 b + wave / 4
+      const uint32_t base_lane = incl - own + (sub > 0 ? c4.x : 0u) + (sub > 1 ? c4.y : 0u) +
+                                 (sub > 2 ? c4.z : 0u);
+      int tid_w = 4 * tid;
+      asm volatile("" : "+v"(tid_w));  // positions made here, not carried from the top
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(keys[4 * b + e]));
+        uint64_t bs[4], bt[4];
+        uint64_t any = 0ull, anyt = 0ull;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bs[e] = ballot(keys[4 * b + e] > t_sure);
+          bt[e] = TIES ? ballot(keys[4 * b + e] == t_tie) : 0ull;
+          any |= bs[e];
+          anyt |= bt[e];
+        }
+        if ((any | anyt) == 0ull) continue;
+        const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)base_lane, 4 * b + (wave >> 2));
+        int s_before = sure0 + (int)(base & 0xFFFFu), t_before = tie0 + (int)(base >> 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_before += lanes_below(bs[e]);
+        if (TIES && anyt != 0ull) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t_before += lanes_below(bt[e]);
+        }
+        const int i0 = tid_w + kBlock * b + (STREAM ? sg * (kBlock * NB) : 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t key = keys[4 * b + e];
+          const bool sure = key > t_sure, tie = TIES && key == t_tie;
+          const bool keep = sure || (tie && t_before < need);
+          if (keep) out[s_before + (TIES ? min(t_before, need) : 0)] = i0 + e;
+          s_before += sure ? 1 : 0;
+          if (TIES) t_before += tie ? 1 : 0;
+          if (kept) {
+            const bool cand = key - 1u < kProtKey - 1u;
+            count_kept_steps(kept, nsteps, (keep && cand) ? sid[i0 + e] : -1, lane);
+          }
+        }
+      }
+      if (STREAM) {
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        sure0 += (int)(all & 0xFFFFu);  // at most 32768 tokens a segment: both halves fit
+        tie0 += (int)(all >> 16);
+      }
+    });
+  }
+
+  __device__ __forceinline__ void run(const SelectArgs& a, const RowSetup& r, int plan_before) const {
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    Keys keys;
+    if constexpr (!STREAM) load_keys<NB>(P, prot, ns, keys);
+    // A lower bound for tau: each thread holding at least m candidates has m
+    // of them at or above its m-th largest, so at least m times as many
+    // candidates as there are such threads lie at or above the smallest of
+    // those m-th largest keys; when ktake is within that number, tau lies there
+    // too and the search skips every key below it. m = 1, 2, 4 or 8, the least
+    // for which the budget can be within the bound.
+    const int m = r.B <= kThreads ? 1 : (r.B <= 2 * kThreads ? 2 : (r.B <= 4 * kThreads ? 4 : 8));
+    int npr = 0;  // wave total
+    uint32_t kmax1, mth1;
+    if (m == 1) survey<1>(keys, npr, kmax1, mth1);
+    else if (m == 2) survey<2>(keys, npr, kmax1, mth1);
+    else if (m == 4) survey<4>(keys, npr, kmax1, mth1);
+    else survey<8>(keys, npr, kmax1, mth1);
+    const bool has = mth1 > 1u;  // this thread holds at least m candidates
+    const uint32_t nthr = (uint32_t)__popcll(ballot(has));
+    kmax1 = wave_extreme<true>(kmax1);
+    const uint32_t tmin = wave_extreme<false>(has ? mth1 - 1u : 0xFFFFFFFFu);
+    reinterpret_cast<uint2*>(sh.hist)[tid] = make_uint2(0u, 0u);
+    if (lane == 0) {
+      sh.red[0][wave] = (uint32_t)npr;
+      sh.red[1][wave] = kmax1;
+      sh.red[2][wave] = tmin;
+      sh.red[3][wave] = nthr;
+    }
+    __syncthreads();
+    // the four results at once, one per row of 16 lanes: sums in rows 0 and 3,
+    // maxima in rows 1 and 2 (of the complement for the minimum)
+    const int row16 = lane >> 4;
+    uint32_t v = (&sh.red[0][0])[lane];
+    if (row16 == 2) v = ~v;
+    const bool sums = row16 == 0 || row16 == 3;
+    auto fold = [&](int t) { v = sums ? v + (uint32_t)t : max(v, (uint32_t)t); };
+    fold(__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    fold(__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
+    fold(__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));  // row_shr:4
+    fold(__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));  // row_shr:8
+    npr = __builtin_amdgcn_readlane((int)v, 15);
+    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readlane((int)v, 31) - 1u;  // with candidates
+    const uint32_t bound = ~(uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+    const int nthr_all = __builtin_amdgcn_readlane((int)v, 63);
+    const int ktake = min(r.B, npr);
+    const bool take_all = ktake == npr;
+    if (r.lh == 0) write_retained(a, r.s, plan_before, r.ns, npr, r.B);
+
+    uint32_t tau = 0u;
+    int need = 0;
+    if (!take_all) {
+      uint32_t lbound = bound;  // tau >= lbound
+      if (ktake > m * nthr_all) {  // no bound: the smallest candidate key
+        uint32_t lowest = 0xFFFFFFFFu;
+        each(keys, [&](int) __attribute__((always_inline)) {
+#pragma unroll
+          for (int j = 0; j < NK; ++j) lowest = min(lowest, keys[j] - 1u);  // 0 wraps to the top
+        });
+        lowest = wave_extreme<false>(lowest);
+        __syncthreads();  // sh.red is read
+        if (lane == 0) sh.red[0][wave] = lowest;
+        __syncthreads();
+        lbound = wave_extreme<false>(sh.red[0][lane & (kWaves - 1)]) + 1u;
+      }
+      if (lbound == kmax) {
+        tau = kmax;  // every candidate from the bound up ties
+        need = ktake;
+      } else {
+        search(keys, lbound, kmax - lbound, ktake, tau, need);
+      }
+    }
+    // keys above tau (0: every token) are kept, and the first `need` equal to it
+    if (need > 0) write_out<true>(keys, tau, need);
+    else write_out<false>(keys, tau, 0);
+  }
+};
+
+template <int NB, bool STREAM>
+__device__ __forceinline__ void run_row(const SelectArgs& a, const RowSetup& r, int plan_before,
+                                        Scratch& sh) {
+  const size_t row = (size_t)r.lh * a.ntot + r.seq0;
+  const Row<NB, STREAM> w{sh,           a.scores + row, a.prot + r.seq0, a.step_ids + r.seq0,
+                          a.idx + row, r.kept,         r.ns,            r.nsteps};
+  w.run(a, r, plan_before);
+}
+
+// Rows of up to NB blocks: the code for the least of 1, 2, 4, .. NB blocks that
+// holds this row.
+template <int NB>
+__device__ __forceinline__ void select_row(const SelectArgs& a, const RowSetup& r, int plan_before,
+                                           Scratch& sh) {
+  if constexpr (NB > 1) {
+    if (r.ns <= kBlock * (NB / 2)) {
+      select_row<NB / 2>(a, r, plan_before, sh);
+      return;
+    }
+  }
+  run_row<NB, false>(a, r, plan_before, sh);
+}
+
+template <int NB>
+__global__ __launch_bounds__(kThreads) void select_cached_kernel(SelectArgs a) {
+  __shared__ __attribute__((aligned(16))) Scratch sh;
+  const RowSetup r = row_setup(a);
+  const int plan_before = r.lh == 0 ? retained_between(a, 0, r.s, sh.wtot) : 0;
+  select_row<NB>(a, r, plan_before, sh);
+}
+
+// Rows past 65536 tokens (and the shorter ones beside them) from memory.
+__global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectArgs a) {
+  __shared__ __attribute__((aligned(16))) Scratch sh;
+  const RowSetup r = row_setup(a);
+  const int plan_before = r.lh == 0 ? retained_between(a, 0, r.s, sh.wtot) : 0;
+  if (r.ns <= kBlock * kStreamBlocks) {
+    select_row<kStreamBlocks>(a, r, plan_before, sh);
+    return;
+  }
+  run_row<kStreamBlocks, true>(a, r, plan_before, sh);
 }
 
 }  // namespace
 
+// The least kernel that holds the longest row: code for more blocks takes more
+// registers (84 for 8 blocks against 46 for up to 4, which lets two workgroups
+// share a CU). Past 16 blocks the keys do not fit the register file.
 hipError_t launch_select(const SelectArgs& a, hipStream_t st) {
   if (a.S * a.LH == 0) {
     hipLaunchKernelGGL(retained_plan_kernel, dim3(1), dim3(kThreads), 0, st, a);
-  } else {
-    if (a.max_len <= kThreads * kCached)
-      hipLaunchKernelGGL(select_cached_kernel, dim3(a.S * a.LH), dim3(kThreads), 0, st, a);
-    else
-      hipLaunchKernelGGL(select_stream_kernel, dim3(a.S * a.LH), dim3(kThreads), 0, st, a);
+    return hipGetLastError();
   }
+  const dim3 grid((unsigned)a.S * (unsigned)a.LH), block(kThreads);
+  const int blocks = (a.max_len + kBlock - 1) / kBlock;
+  if (blocks <= 1) hipLaunchKernelGGL(select_cached_kernel<1>, grid, block, 0, st, a);
+  else if (blocks <= 4) hipLaunchKernelGGL(select_cached_kernel<4>, grid, block, 0, st, a);
+  else if (blocks <= 8) hipLaunchKernelGGL(select_cached_kernel<8>, grid, block, 0, st, a);
+  else if (blocks <= kCachedBlocks)
+    hipLaunchKernelGGL(select_cached_kernel<kCachedBlocks>, grid, block, 0, st, a);
+  else hipLaunchKernelGGL(select_stream_kernel, grid, block, 0, st, a);
   return hipGetLastError();
 }
 
