@@ -780,8 +780,11 @@ hipError_t launch_fuse(const FuseArgs& a, hipStream_t st) {
   // sequences 152 -> 118 us; with one round (32 x 8 rows of one 32k sequence)
   // the per-sequence kernel stays ahead, 37 against 41 us.
   // Sequences with more than 4096 steps take the spread path too: the
-  // per-sequence kernels stage every step utility in LDS.
-  if (!a.stats && (a.S * a.LH > 256 || a.max_steps > 4096)) {
+  // per-sequence kernels stage every step utility in LDS. So do sequences past
+  // the 32768 positions that fuse_batched_kernel holds: fuse_stream_kernel walks
+  // them 1024 positions at a time, two barriers each (64 rows of 131071
+  // positions: 416 us, spread 34 us).
+  if (!a.stats && (a.S * a.LH > 256 || a.max_steps > 4096 || a.max_len > kBatch * kMaxBatches)) {
     if (a.total_chunks == 0) return hipSuccess;
     const unsigned row_groups = (unsigned)((a.LH + kPrRows - 1) / kPrRows);
     const dim3 grid(row_groups * (unsigned)a.total_chunks);
