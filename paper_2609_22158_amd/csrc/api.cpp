@@ -354,9 +354,9 @@ int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const void*
   return STEPKV_OK;
 }
 
-int run_priority(const stepkv_problem* pb, const stepkv_params* prm, const float* sal,
-                 const int32_t* step_ids, const uint8_t* protected_mask, const float* util,
-                 float* scores, stepkv_step_stat* stats, hipStream_t st) {
+FuseArgs fuse_args(const stepkv_problem* pb, const stepkv_params* prm, const float* sal,
+                   const int32_t* step_ids, const uint8_t* protected_mask, const float* util,
+                   float* scores, stepkv_step_stat* stats) {
   FuseArgs fa;
   fa.sal = sal;
   fa.cu_seqlens = pb->cu_seqlens;
@@ -377,7 +377,37 @@ int run_priority(const stepkv_problem* pb, const stepkv_params* prm, const float
   fa.total_chunks = prio_chunks(pb->cu_seqlens_host, pb->num_seqs);
   fa.alpha = prm->alpha;
   fa.beta = prm->beta;
-  return hip_status(launch_fuse(fa, st));
+  return fa;
+}
+
+int run_priority(const stepkv_problem* pb, const stepkv_params* prm, const float* sal,
+                 const int32_t* step_ids, const uint8_t* protected_mask, const float* util,
+                 float* scores, stepkv_step_stat* stats, hipStream_t st) {
+  return hip_status(
+      launch_fuse(fuse_args(pb, prm, sal, step_ids, protected_mask, util, scores, stats), st));
+}
+
+SelectArgs select_args(const stepkv_problem* pb, const float* scores,
+                       const uint8_t* protected_mask, const int32_t* step_ids, int32_t budget,
+                       const int32_t* budgets, int32_t* idx, int32_t* cu_retained,
+                       int32_t* kept_per_step) {
+  SelectArgs a;
+  a.scores = scores;
+  a.prot = protected_mask;
+  a.step_ids = step_ids;
+  a.cu_seqlens = pb->cu_seqlens;
+  a.cu_steps = pb->cu_steps;
+  a.budgets = budgets;
+  a.idx = idx;
+  a.cu_retained = cu_retained;
+  a.kept = kept_per_step;
+  a.S = pb->num_seqs;
+  a.LH = pb->num_layers * pb->num_kv_heads;
+  a.ntot = pb->cu_seqlens_host[pb->num_seqs];
+  a.total_steps = pb->cu_steps_host[pb->num_seqs];
+  a.budget = std::max(budget, 1);
+  a.max_len = max_seqlen(pb);
+  return a;
 }
 
 // The priority reads the saliency around each position while other
@@ -695,22 +725,8 @@ int stepkv_select(const stepkv_problem* pb, const float* scores, const uint8_t* 
   if (!scores || !protected_mask || !idx || !cu_retained) return STEPKV_EINVAL;
   if (kept_per_step && !step_ids) return STEPKV_EINVAL;
   if (!budgets && budget < 1) return STEPKV_EINVAL;
-  SelectArgs a;
-  a.scores = scores;
-  a.prot = protected_mask;
-  a.step_ids = step_ids;
-  a.cu_seqlens = pb->cu_seqlens;
-  a.cu_steps = pb->cu_steps;
-  a.budgets = budgets;
-  a.idx = idx;
-  a.cu_retained = cu_retained;
-  a.kept = kept_per_step;
-  a.S = pb->num_seqs;
-  a.LH = pb->num_layers * pb->num_kv_heads;
-  a.ntot = pb->cu_seqlens_host[pb->num_seqs];
-  a.total_steps = pb->cu_steps_host[pb->num_seqs];
-  a.budget = std::max(budget, 1);
-  a.max_len = max_seqlen(pb);
+  const SelectArgs a = select_args(pb, scores, protected_mask, step_ids, budget, budgets, idx,
+                                   cu_retained, kept_per_step);
   return hip_status(launch_select(a, static_cast<hipStream_t>(stream)));
 }
 
@@ -769,8 +785,15 @@ int stepkv_compress(const stepkv_problem* pb, const stepkv_params* prm, const vo
     float* sal = reinterpret_cast<float*>(ws + layout(pb, plan_saliency(pb)).sal);
     rc = run_saliency(pb, prm, q_win, k, sal, ws, st,
                       lse_win ? SaliencyMode::kFromLse : SaliencyMode::kBoth, lse_win);
-    if (rc == STEPKV_OK)
-      rc = run_priority(pb, prm, sal, step_ids, protected_mask, step_utility, P, nullptr, st);
+    if (rc != STEPKV_OK) return rc;
+    const FuseArgs fa = fuse_args(pb, prm, sal, step_ids, protected_mask, step_utility, P, nullptr);
+    if (rank_fits(fa)) {
+      rc = hip_status(launch_rank(fa, select_args(pb, P, protected_mask, step_ids, budget, budgets,
+                                                  I, cu_retained, nullptr), st));
+      if (rc != STEPKV_OK) return rc;
+      return stepkv_compact(pb, k, v, I, cu_retained, out_rows, k_out, v_out, stream);
+    }
+    rc = hip_status(launch_fuse(fa, st));
     if (rc != STEPKV_OK) return rc;
   }
   rc = stepkv_select(pb, P, protected_mask, step_ids, budget, budgets, I, cu_retained, nullptr,

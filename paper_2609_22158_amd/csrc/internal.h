@@ -105,6 +105,10 @@ struct SelectArgs {
   int S, LH, ntot, total_steps, budget, max_len;
 };
 hipError_t launch_select(const SelectArgs& a, hipStream_t st);
+// Priority and selection in one launch (f.scores and a.scores the same rows,
+// no statistics, no kept_per_step), for problems that rank_fits.
+bool rank_fits(const FuseArgs& f);
+hipError_t launch_rank(const FuseArgs& f, const SelectArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------- compact
 struct CompactArgs {

@@ -28,6 +28,8 @@
 #include "common.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace stepkv {
 namespace {
 
@@ -244,6 +246,13 @@ struct Scratch {
   uint32_t nlist;
 };
 
+// Order-preserving key of a score: NaN -> -inf and -0 -> +0 in float
+// arithmetic, then the sign flip.
+__device__ __forceinline__ uint32_t order_key(float p) {
+  const uint32_t u = __float_as_uint(fmaxf(p, -INFINITY) + 0.0f);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
 // Keys of NB blocks from P and prot (at the first block's base), whose first
 // `rem` positions exist: keys[4 b + e] is position 4096 b + 4 tid + e. Every
 // load of 4 blocks is issued before any is used (8 took 0.4 us more on a row of
@@ -288,11 +297,7 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ P,
     const int left = rem - kBlock * b;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      // NaN -> -inf and -0 -> +0 in float arithmetic, then the sign flip
-      const float q = fmaxf(pv[4 * b + e], -INFINITY) + 0.0f;
-      const uint32_t u = __float_as_uint(q);
-      const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-      keys[4 * b + e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? key : kProtKey;
+      keys[4 * b + e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? order_key(pv[4 * b + e]) : kProtKey;
     }
     if (left < kBlock) {  // uniform: positions past the sequence
 #pragma unroll
@@ -430,8 +435,16 @@ struct Row {
     } while (n > kList);
     each(keys, [&](int) __attribute__((always_inline)) {  // the bin's keys into LDS, in any order
 #pragma unroll
-      for (int j = 0; j < NK; ++j)
-        if (keys[j] - lo <= span) sh.list[atomicAdd(&sh.nlist, 1u)] = keys[j];
+      for (int b = 0; b < NB; ++b) {
+        uint32_t d[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = keys[4 * b + e] - lo;
+        if (min(min(d[0], d[1]), min(d[2], d[3])) <= span) {  // few runs hold one
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (d[e] <= span) sh.list[atomicAdd(&sh.nlist, 1u)] = lo + d[e];
+        }
+      }
     });
     __syncthreads();
     const int nlist = n;
@@ -552,10 +565,10 @@ struct Row {
     });
   }
 
-  __device__ __forceinline__ void run(const SelectArgs& a, const RowSetup& r, int plan_before) const {
+  // The row's selection from its keys (STREAM: read from memory here).
+  __device__ __forceinline__ void run(const SelectArgs& a, const RowSetup& r, int plan_before,
+                                      Keys& keys) const {
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-    Keys keys;
-    if constexpr (!STREAM) load_keys<NB>(P, prot, ns, keys);
     // A lower bound for tau: each thread holding at least m candidates has m
     // of them at or above its m-th largest, so at least m times as many
     // candidates as there are such threads lie at or above the smallest of
@@ -635,7 +648,9 @@ __device__ __forceinline__ void run_row(const SelectArgs& a, const RowSetup& r, 
   const size_t row = (size_t)r.lh * a.ntot + r.seq0;
   const Row<NB, STREAM> w{sh,           a.scores + row, a.prot + r.seq0, a.step_ids + r.seq0,
                           a.idx + row, r.kept,         r.ns,            r.nsteps};
-  w.run(a, r, plan_before);
+  typename Row<NB, STREAM>::Keys keys;
+  if constexpr (!STREAM) load_keys<NB>(w.P, w.prot, w.ns, keys);
+  w.run(a, r, plan_before, keys);
 }
 
 // Rows of up to NB blocks: the code for the least of 1, 2, 4, .. NB blocks that
@@ -672,7 +687,221 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectArgs a) {
   run_row<kStreamBlocks, true>(a, r, plan_before, sh);
 }
 
+// ---------------------------------------------------------------- priority and selection
+// The priority (as the kernels of fuse.hip, value for value) and the selection
+// of one row by one workgroup: the saliency of the row stays in registers, is
+// pooled there (neighbouring runs come from the next lane by DPP and, at the
+// ends of a wave, from LDS) and becomes P, which is written once and ranked from
+// the registers. The row is not read again, and one launch takes the place of
+// two to four. Bound by vector issue on the row's CU (about 55 instructions per
+// position), for short rows by the chain of loads and barriers. Priority and
+// selection before (separate launches) and now: 256 rows of 32768 tokens
+// 33 + 25 -> 27 us, of 16384 22 + 24 -> 19, 8 rows of 8192 10 + 21 -> 10, 2 rows
+// of 1024 9.5 + 20 -> 7.7, 16 sequences of 4k to 32k tokens x 112 heads
+// 98 + 206 -> 152. Rows of up to 8 blocks (more do not fit the registers),
+// pooling windows of up to 9 and up to kRankSteps steps per sequence (the table
+// of step utilities in LDS).
+constexpr int kRankSteps = 4096;
+constexpr int kRankHalf = 4;
+constexpr int kRankBlocks = 8;
+
+// What rank_row holds in place of U for a protected token or a position past
+// the sequence: a NaN that no sum of saliencies produces, passed over by fmaxf.
+constexpr uint32_t kNoU = 0xFFFFFFFFu;
+
+// The masked saliency at the ends of every wave's 256 positions, where the
+// neighbouring wave's pooling reads it: run q of 256 positions is entry q + 1,
+// its first four positions, then its last four; entries 0 and 16 NB + 1 stay 0.
+struct Edges {
+  float4 e[kRankBlocks * kWaves + 2][2];
+};
+
+template <int NB, int HALF, bool FLAGS>
+__device__ __forceinline__ void rank_row(const FuseArgs& f, const SelectArgs& a, const RowSetup& r,
+                                         int plan_before, float* bu_lds, Edges& ed, Scratch& sh) {
+  if constexpr (NB > 1) {
+    if (r.ns <= kBlock * (NB / 2)) {
+      rank_row<NB / 2, HALF, FLAGS>(f, a, r, plan_before, bu_lds, ed, sh);
+      return;
+    }
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int p4 = 4 * tid;
+  const size_t row = (size_t)r.lh * a.ntot + r.seq0;
+  const float* __restrict__ A = f.sal + row;
+  const uint8_t* __restrict__ prot = a.prot + r.seq0;
+  const int st0 = f.cu_steps[r.s], nsteps = f.cu_steps[r.s + 1] - st0;
+
+  // ---- every load of the row, issued before any is used
+  float u[NB][4];  // the saliency, then U
+  uint32_t pw[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int left = r.ns - kBlock * b;  // uniform
+    pw[b] = 0xFFFFFFFFu;                 // past the sequence: not prunable
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[b][e] = 0.f;
+    if (left >= kBlock) {
+      __builtin_memcpy(u[b], A + kBlock * b + p4, 16);
+      __builtin_memcpy(&pw[b], prot + kBlock * b + p4, 4);
+    } else if (left > 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p4 + e < left) {
+          u[b][e] = A[kBlock * b + p4 + e];
+          pw[b] = (pw[b] & ~(0xFFu << (8 * e))) | ((uint32_t)prot[kBlock * b + p4 + e] << (8 * e));
+        }
+      }
+    }
+  }
+  // beta S of every step, and beta 0 for ids out of range
+  for (int k = tid; k <= nsteps; k += kThreads) bu_lds[k] = f.beta * (k < nsteps ? f.util[st0 + k] : 0.f);
+  if (tid < 2) ed.e[tid ? NB * kWaves + 1 : 0][tid ? 0 : 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[b][e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? u[b][e] : 0.f;
+  }
+  const bool edge = lane == 0 || lane == 63;
+  if (HALF > 0) {
+    if (edge) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        ed.e[b * kWaves + wave + 1][lane ? 1 : 0] = make_float4(u[b][0], u[b][1], u[b][2], u[b][3]);
+    }
+    __syncthreads();
+  }
+
+  // ---- pooling in place, left to right as every pooling kernel adds, and the maximum
+  float m = 0.f;  // U >= 0, and Th = 0 everywhere when the maximum is 0
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float v[12];  // positions p4 - 4 .. p4 + 7
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[4 + e] = u[b][e];
+    if (HALF > 0) {
+      float4 h = make_float4(0.f, 0.f, 0.f, 0.f);  // lane 0: the run before, lane 63: the run after
+      if (edge) h = ed.e[b * kWaves + wave + (lane ? 2 : 0)][lane ? 0 : 1];
+      const float he[4] = {h.x, h.y, h.z, h.w};
+      // wave_shr:1 and wave_shl:1; the lane without a source keeps its halo
+#pragma unroll
+      for (int e = 4 - HALF; e < 4; ++e)
+        v[e] = __int_as_float(__builtin_amdgcn_update_dpp(
+            __float_as_int(he[e]), __float_as_int(v[4 + e]), 0x138, 0xf, 0xf, false));
+#pragma unroll
+      for (int e = 0; e < HALF; ++e)
+        v[8 + e] = __int_as_float(__builtin_amdgcn_update_dpp(
+            __float_as_int(he[e]), __float_as_int(v[4 + e]), 0x130, 0xf, 0xf, false));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float acc = v[4 + e - HALF];
+#pragma unroll
+      for (int o = 1; o <= 2 * HALF; ++o) acc += v[4 + e - HALF + o];
+      u[b][e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? acc : __uint_as_float(kNoU);
+      m = fmaxf(m, u[b][e]);
+    }
+  }
+  // step ids, on their way while the maximum is reduced
+  const int32_t* __restrict__ sid = a.step_ids + r.seq0;
+  int kk[NB][4];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int left = r.ns - kBlock * b, i0 = kBlock * b + p4;  // left: uniform
+#pragma unroll
+    for (int e = 0; e < 4; ++e) kk[b][e] = -1;
+    if (left >= kBlock) {
+      __builtin_memcpy(kk[b], sid + i0, 16);
+    } else if (left > 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (p4 + e < left) kk[b][e] = sid[i0 + e];
+    }
+  }
+  // non-negative floats order as their bits
+  const uint32_t wm = wave_extreme<true>(__float_as_uint(m));
+  if (lane == 0) sh.wtot[wave] = wm;
+  __syncthreads();
+  const float M = __uint_as_float(wave_extreme<true>(sh.wtot[lane & (kWaves - 1)]));
+  const float inv = M > 0.f ? 1.0f / M : 0.f;
+
+  // ---- P, written once; its keys take the place of U
+  float* __restrict__ out = f.scores + row;
+  typename Row<NB, false>::Keys keys;
+  uint64_t bad_id = 0ull, bad_nf = 0ull;  // wave masks of STEPKV_FLAG_* conditions
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int left = r.ns - kBlock * b, i0 = kBlock * b + p4;
+    float pv[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool pr = __float_as_uint(u[b][e]) != kNoU;
+      const float bu = bu_lds[min((uint32_t)kk[b][e], (uint32_t)nsteps)];
+      const float p = fmaf(f.alpha, u[b][e] * inv, bu);
+      if (FLAGS) {
+        bad_id |= ballot(pr && (uint32_t)kk[b][e] >= (uint32_t)nsteps);
+        bad_nf |= ballot(pr && !finite(p));
+      }
+      pv[e] = pr ? p : -INFINITY;
+      keys[4 * b + e] = pr ? order_key(p) : kProtKey;
+    }
+    if (FLAGS) asm volatile("" : "+s"(bad_id), "+s"(bad_nf));  // no ballot outlives its block
+    if (left >= kBlock) {
+      __builtin_memcpy(out + i0, pv, 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p4 + e < left) out[i0 + e] = pv[e];
+        else keys[4 * b + e] = 0u;  // past the sequence
+      }
+    }
+  }
+  if (FLAGS) report_masks(f.status, bad_id, bad_nf);
+  const Row<NB, false> w{sh, nullptr, prot, sid, a.idx + row, nullptr, r.ns, 0};
+  w.run(a, r, plan_before, keys);
+}
+
+template <int NB, int HALF, bool FLAGS>
+__global__ __launch_bounds__(kThreads) void rank_kernel(FuseArgs f, SelectArgs a) {
+  __shared__ __attribute__((aligned(16))) Scratch sh;
+  __shared__ Edges ed;
+  extern __shared__ float bu_lds[];  // [max_steps + 1]
+  const RowSetup r = row_setup(a);
+  const int plan_before = r.lh == 0 ? retained_between(a, 0, r.s, sh.wtot) : 0;
+  rank_row<NB, HALF, FLAGS>(f, a, r, plan_before, bu_lds, ed, sh);
+}
+
 }  // namespace
+
+bool rank_fits(const FuseArgs& f) {
+  return !f.stats && f.half <= kRankHalf && f.max_steps <= kRankSteps &&
+         f.max_len <= kBlock * kRankBlocks;
+}
+
+hipError_t launch_rank(const FuseArgs& f, const SelectArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)a.S * (unsigned)a.LH), block(kThreads);
+  const size_t dyn = sizeof(float) * ((size_t)f.max_steps + 1);
+  const int blocks = (a.max_len + kBlock - 1) / kBlock;
+  auto go = [&](auto half_c, auto flags_c) {
+    constexpr int H = decltype(half_c)::value;
+    constexpr bool F = decltype(flags_c)::value;
+    if (blocks <= 1) hipLaunchKernelGGL((rank_kernel<1, H, F>), grid, block, dyn, st, f, a);
+    else if (blocks <= 4) hipLaunchKernelGGL((rank_kernel<4, H, F>), grid, block, dyn, st, f, a);
+    else hipLaunchKernelGGL((rank_kernel<kRankBlocks, H, F>), grid, block, dyn, st, f, a);
+  };
+  auto with_flags = [&](auto half_c) {
+    if (f.status) go(half_c, std::true_type{});
+    else go(half_c, std::false_type{});
+  };
+  switch (f.half) {
+    case 0: with_flags(std::integral_constant<int, 0>{}); break;
+    case 1: with_flags(std::integral_constant<int, 1>{}); break;
+    case 2: with_flags(std::integral_constant<int, 2>{}); break;
+    case 3: with_flags(std::integral_constant<int, 3>{}); break;
+    default: with_flags(std::integral_constant<int, 4>{}); break;
+  }
+  return hipGetLastError();
+}
 
 // The least kernel that holds the longest row: code for more blocks takes more
 // registers (84 for 8 blocks against 46 for up to 4, which lets two workgroups

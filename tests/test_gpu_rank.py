@@ -1,0 +1,54 @@
+"""The one-launch priority and selection of stepkv_compress against stepkv_score and
+stepkv_select, bit for bit: row lengths around the waves' 256 positions and the blocks of 4096,
+pooling windows 1 to 9 (in registers) and 11 (the separate kernels), protected tokens and
+out-of-range step ids anywhere, a NaN key, and the status word's flags."""
+import numpy as np
+import pytest
+
+from tests.gpu_cases import gpu_utilities, log
+from synth import make_workload
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = {"short": [1, 0, 3, 255, 256, 257, 1000], "block": [4095, 4096, 4097, 8191],
+           "blocks": [8192, 8193, 16384], "rows": [16385, 32768, 5]}
+
+
+@pytest.mark.parametrize("pool", [1, 3, 5, 7, 9, 11])
+@pytest.mark.parametrize("lengths", list(LENGTHS))
+def test_compress_equals_score_and_select(lengths, pool):
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    w = make_workload("ragged16", seqlens=LENGTHS[lengths], num_layers=2, protected_len=0,
+                      budget=700)
+    pb = B.Problem.from_workload(w)
+    rng = np.random.default_rng(pool)
+    prot = (rng.random(w.total_tokens) < 0.03).astype(np.uint8)
+    ids = w.step_ids.copy()
+    ids[rng.random(w.total_tokens) < 0.001] = 1 << 20
+    ids[rng.random(w.total_tokens) < 0.001] = -7
+    kk = w.k.copy()
+    if pool == 3:
+        kk[0, 0, w.total_tokens // 2] = 0x7FC0  # a NaN key in one row
+    q, k, v = (B.bf16_from_bits(x) for x in (w.q_win, kk, w.v))
+    sid, pdev = torch.from_numpy(ids).cuda(), torch.from_numpy(prot).cuda()
+    util = torch.from_numpy(gpu_utilities(w)).cuda()
+    prm = B.Params(pool_kernel=pool, alpha=0.7, beta=0.3)
+    rows = int(pb.retained_rows(prot, w.budget)[-1])
+    log(f"[rank {lengths} pool={pool}] score and select")
+    P = B.score(pb, q, k, sid, pdev, util, prm)["scores"]
+    idx, cu, _ = B.select(pb, P, pdev, sid, w.budget)
+    flags = pb.status(clear=True)
+    log(f"[rank {lengths} pool={pool}] compress")
+    res = B.compress(pb, q, k, v, sid, pdev, util, w.budget, rows, prm)
+    assert pb.status(clear=True) == flags
+    assert bool(flags & B.FLAG_NONFINITE) == (pool == 3)
+    assert np.array_equal(res["scores"].cpu().numpy().view(np.uint32), P.cpu().numpy().view(np.uint32))
+    assert np.array_equal(res["cu_retained"].cpu().numpy(), cu.cpu().numpy())
+    c, got, want = cu.cpu().numpy(), res["idx"].cpu().numpy(), idx.cpu().numpy()
+    for s in range(w.num_seqs):
+        a = int(w.cu_seqlens[s])
+        n = int(c[s + 1] - c[s])
+        assert np.array_equal(got[:, :, a:a + n], want[:, :, a:a + n])

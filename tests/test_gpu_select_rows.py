@@ -7,9 +7,9 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_cases import log
+from tests.gpu_cases import log
 from synth import make_workload
-from test_gpu_parity import _special_scores
+from tests.test_gpu_parity import _special_scores
 
 pytestmark = pytest.mark.gpu
 
