@@ -149,7 +149,9 @@ typedef struct stepkv_params {
    * its row LSEs so that K is read again from the Infinity Cache, when K
    * exceeds 192 MiB and there are at least twice as many chunks as resident
    * workgroups, otherwise one launch per sweep; 1 = one launch per sweep;
-   * 2 = one launch. Calls given the row LSEs run one sweep either way. */
+   * 2 = one launch. With at most 8 window rows (W * G), 0 reads K once and
+   * keeps its logits in the workspace. Calls given the row LSEs run one sweep
+   * either way. */
   int32_t saliency_schedule;
 } stepkv_params;
 
@@ -262,7 +264,8 @@ int stepkv_text_cues(const char* text, int64_t text_len, uint64_t* cues, int32_t
 
 /* ---------------------------------------------------------------- device passes */
 /* Bytes of device workspace stepkv_score needs for this problem (0 when the
- * problem is invalid). The workspace needs no initialisation and is
+ * problem is invalid); with at most 8 window rows it holds 16 or 32 bytes of
+ * logits per token, layer and KV head. The workspace needs no initialisation and is
  * scratch between calls; 256-byte alignment is required. */
 size_t stepkv_score_workspace_bytes(const stepkv_problem* pb);
 
@@ -357,8 +360,10 @@ int stepkv_score(const stepkv_problem* pb, const stepkv_params* prm, const void*
  * (fp32 [L][Hkv][Ntot], the A buffer the sweeps write) is required here.
  * Same arguments, results and errors as stepkv_score otherwise, plus
  * STEPKV_ESCRATCH when the problem needs more than the buffer
- * (stepkv_saliency_workspace_bytes(pb) > STEPKV_STATIC_SCRATCH_BYTES), found
- * before anything is launched. The first call on a device looks the buffer's
+ * (stepkv_saliency_workspace_bytes(pb) > STEPKV_STATIC_SCRATCH_BYTES, the
+ * logits of few window rows left out: where those do not fit, K is read twice
+ * and the results agree with stepkv_score to rounding), found before anything
+ * is launched. The first call on a device looks the buffer's
  * address up (EHIP if that fails). Every call on one GPU shares its buffer,
  * which keeps the last call's contents (no part of it needs to start at
  * zero): calls that overlap on one GPU, on different streams or threads,

@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libstepkv.so")
 C_DEMO_SRC = os.path.join(ROOT, "tests", "c_abi", "compress_demo.c")
 C_DEMO = os.path.join(ROOT, "tests", "c_abi", "compress_demo")
 
-SOURCES = ["api.cpp", "step_text.cpp", "saliency.hip", "fuse.hip", "select.hip", "compact.hip",
+SOURCES = ["api.cpp", "step_text.cpp", "saliency.hip", "fewrows.hip", "fuse.hip", "select.hip", "compact.hip",
            "decode.hip", "scratch.hip", "probe.hip"]
 ARCH = "gfx950"
 

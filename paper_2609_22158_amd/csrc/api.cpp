@@ -74,12 +74,17 @@ struct SaliencyPlan {
   // both sweeps in one launch: chunk, chunk count and row-LSE lead (items)
   int fused_chunk, fused_total_chunks, fused_lag;
   bool fused_pays;  // the schedule chosen per problem (stepkv_params.saliency_schedule 0)
+  // few window rows: K read once with its logits kept (schedule 0 only)
+  bool few;
+  int few_chunk, few_total_chunks;
+  int64_t few_slots;  // logit slots per head
 };
 
 // Window rows per pair of sweeps (the MFMA tiling holds at most 256).
 constexpr int kRowGroup = 256;
 
-SaliencyPlan plan_saliency(const stepkv_problem* pb) {
+// may_keep: whether the workspace may hold the logits of few window rows.
+SaliencyPlan plan_saliency(const stepkv_problem* pb, bool may_keep = true) {
   SaliencyPlan p;
   p.R = window_rows(pb);
   p.rows_pad = saliency_rows_pad(std::min(p.R, kRowGroup));  // the first (widest) group
@@ -132,11 +137,19 @@ SaliencyPlan plan_saliency(const stepkv_problem* pb) {
   // are enough chunks for the row-LSE items to run a round ahead.
   const int64_t k_bytes = lh * (int64_t)pb->cu_seqlens_host[pb->num_seqs] * 2 * pb->head_dim;
   p.fused_pays = k_bytes > kFusedReuseBytes && lh * p.fused_total_chunks >= 2 * kSalSlots;
+  // Few rows: a chunk (a multiple of 64 keys, a tile per wave) for about twelve
+  // workgroups per compute unit, six of which are resident.
+  p.few = may_keep && few_rows(p.R);
+  const int64_t ntot = pb->cu_seqlens_host[pb->num_seqs];
+  p.few_chunk = (int)std::min<int64_t>(
+      1024, std::max<int64_t>(128, (lh * ntot / (12 * 256) + 63) / 64 * 64));
+  p.few_total_chunks = (int)chunks_for(p.few_chunk);
+  p.few_slots = (ntot + 15) / 16 * 16 + 16 * (int64_t)pb->num_seqs;
   return p;
 }
 
 struct WsLayout {
-  size_t partial, lse, cnt, sal, total;
+  size_t partial, lse, cnt, logits, sal, total;
 };
 
 WsLayout layout(const stepkv_problem* pb, const SaliencyPlan& p) {
@@ -144,13 +157,16 @@ WsLayout layout(const stepkv_problem* pb, const SaliencyPlan& p) {
   const size_t ntot = (size_t)pb->cu_seqlens_host[pb->num_seqs];
   WsLayout w;
   size_t off = 0;
-  w.partial = off;  // sized for the longer chunk list of the two plans
+  w.partial = off;  // sized for the longest chunk list of the plans
   off = align_up(off + sizeof(float) * 2 * lh *
-                           std::max(p.total_chunks, p.fused_total_chunks) * p.rows_pad);
+                           std::max((size_t)std::max(p.total_chunks, p.fused_total_chunks) * p.rows_pad,
+                                    p.few ? (size_t)p.few_total_chunks * 16 : 0));
   w.lse = off;
   off = align_up(off + sizeof(float) * pb->num_seqs * lh * p.rows_pad);
   w.cnt = off;  // per (sequence, head) counters of the one-launch sweeps
   off = align_up(off + sizeof(int32_t) * pb->num_seqs * lh);
+  w.logits = off;
+  if (p.few) off = align_up(off + sizeof(float) * lh * p.few_slots * 4 * few_rows_quads(p.R));
   w.sal = off;
   off = align_up(off + sizeof(float) * lh * ntot);
   w.total = off;
@@ -300,8 +316,8 @@ int max_steps_per_seq(const stepkv_problem* pb) {
 int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
                  const void* k, float* sal, uint8_t* ws, hipStream_t st,
                  SaliencyMode mode = SaliencyMode::kBoth, const float* lse_in = nullptr,
-                 float* lse_out = nullptr) {
-  const SaliencyPlan plan = plan_saliency(pb);
+                 float* lse_out = nullptr, bool may_keep = true) {
+  const SaliencyPlan plan = plan_saliency(pb, may_keep);
   const WsLayout w = layout(pb, plan);
   const int d = pb->head_dim;
   SaliencyArgs sa;
@@ -324,8 +340,12 @@ int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const void*
   sa.status = pb->status;
   const bool fused = mode == SaliencyMode::kBoth &&
                      (prm->saliency_schedule == 0 ? plan.fused_pays : prm->saliency_schedule == 2);
-  sa.chunk = fused ? plan.fused_chunk : plan.chunk;
-  sa.total_chunks = fused ? plan.fused_total_chunks : plan.total_chunks;
+  const bool few = plan.few && mode == SaliencyMode::kBoth && prm->saliency_schedule == 0;
+  sa.chunk = few ? plan.few_chunk : (fused ? plan.fused_chunk : plan.chunk);
+  sa.total_chunks =
+      few ? plan.few_total_chunks : (fused ? plan.fused_total_chunks : plan.total_chunks);
+  sa.logits = few ? reinterpret_cast<float*>(ws + w.logits) : nullptr;
+  sa.logit_slots = plan.few_slots;
   sa.unit_cnt = fused ? reinterpret_cast<int*>(ws + w.cnt) : nullptr;
   sa.lag = plan.fused_lag;
   // the chunk lookup's argument tables (used when S <= kArgSeqs)
@@ -340,6 +360,13 @@ int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const void*
   }
   const double scale = prm->scale > 0.0f ? (double)prm->scale : 1.0 / std::sqrt((double)d);
   sa.c = (float)(scale * 1.4426950408889634);  // log2(e)
+  if (few) {
+    sa.row0 = 0;
+    sa.R = plan.R;
+    sa.rows_pad = plan.rows_pad;
+    sa.accumulate = 0;
+    return hip_status(launch_few_rows(sa, d, st));
+  }
   // Window rows in groups of at most 256, one pair of sweeps per group: a
   // row's LSE needs only its own logits, and the column sums of the later
   // groups add to the first group's (the workspace regions are reused).
@@ -550,13 +577,16 @@ int stepkv_score_noalloc(const stepkv_problem* pb, const stepkv_params* prm, con
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  // the sweeps' workspace (everything but the saliency buffer, which the caller passes)
-  if (layout(pb, plan_saliency(pb)).sal > kStaticScratchBytes) return STEPKV_ESCRATCH;
+  // the sweeps' workspace (everything but the saliency buffer, which the caller
+  // passes), with the logits of few window rows where they fit
+  const bool may_keep = layout(pb, plan_saliency(pb)).sal <= kStaticScratchBytes;
+  if (layout(pb, plan_saliency(pb, may_keep)).sal > kStaticScratchBytes) return STEPKV_ESCRATCH;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
   void* ws = nullptr;
   if (static_scratch(&ws) != hipSuccess || !ws) return STEPKV_EHIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  rc = run_saliency(pb, prm, q_win, k, saliency, static_cast<uint8_t*>(ws), st);
+  rc = run_saliency(pb, prm, q_win, k, saliency, static_cast<uint8_t*>(ws), st,
+                    SaliencyMode::kBoth, nullptr, nullptr, may_keep);
   if (rc != STEPKV_OK) return rc;
   return run_priority(pb, prm, saliency, step_ids, protected_mask, step_utility, scores,
                       step_stats, st);

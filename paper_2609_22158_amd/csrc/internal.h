@@ -33,6 +33,10 @@ struct SaliencyArgs {
   int* unit_cnt;
   int lag;
   uint32_t* status;  // device status word (STEPKV_FLAG_*) or null
+  // few window rows: the logits [L*Hkv][logit_slots][4 * few_rows_quads(R)],
+  // and partial is [L*Hkv][total_chunks][16]
+  float* logits;
+  int64_t logit_slots;
   // Batches of at most kArgSeqs sequences also pass cu_seqlens and each
   // sequence's first chunk (at this launch's chunk size) by value: a workgroup
   // then finds its chunk with scalar loads of its arguments, where a read of
@@ -51,6 +55,13 @@ int saliency_tile_keys(int R);
 // LSE, exported to lse_out), or the second one only (from lse_in).
 enum class SaliencyMode { kBoth, kLseOnly, kFromLse };
 hipError_t launch_saliency(const SaliencyArgs& a, int d, SaliencyMode mode, hipStream_t st);
+
+// Few window rows (all of them in one group): K read once and the logits kept
+// (both sweeps' work; no row LSE is exported). few_rows: whether R rows take
+// this form.
+bool few_rows(int R);
+int few_rows_quads(int R);
+hipError_t launch_few_rows(const SaliencyArgs& a, int d, hipStream_t st);
 
 // ---------------------------------------------------------------- fuse
 struct FuseArgs {
