@@ -3,7 +3,7 @@
 // accumulation (the consumer of the compacted cache, Sec. 3).
 //
 // decode_mfma_kernel: one workgroup per (layer, KV head, sequence, split of
-// 512 or 1024 retained rows) serves all G <= 16 query heads of the KV head, so K and V
+// 64 to 1024 retained rows) serves all G <= 16 query heads of the KV head, so K and V
 // are read once: q . k and p V for the whole query group on MFMA with an
 // exact online softmax per head between them, several 16-row tiles in flight
 // per wave; decode_combine_kernel merges the splits. decode_simple_kernel
@@ -412,68 +412,158 @@ void decode_mfma_kernel(DecodeArgs a) {
   }
 }
 
-// out[l][s][hq] = merge of the splits of sequence s (o / z; zero rows give 0).
-template <int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
+// out[l][s][hq] = merge of the splits of sequence s (o / z; zero rows give 0),
+// for the G query heads of a KV head (HEADS_G) or for one of them per workgroup:
+//   M and Z per head: a lane per split; the weights 2^(m - M) of up to
+//   kBlockSplits splits at a time go to LDS;
+//   O: a thread per (head, dim) adds the splits' weighted partial outputs, in
+//   order; with one head per workgroup THREADS / D groups of threads share the
+//   splits and their sums are added in group order.
+// The first splits' partial outputs are loaded before the weights are known, so
+// that a merge of few splits waits for memory once. The chain of loads bounds
+// it: 24 splits of one sequence with a thread per dim and eight splits at a time
+// took 5 us more than 3 splits, now nothing measurable.
+constexpr int kBlockSplits = 64;
+
+template <int D, int THREADS, bool HEADS_G>
+__global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
   constexpr int ST = D + 2;
-  const int hq = blockIdx.x % a.Hq;
-  const int s = (blockIdx.x / a.Hq) % a.S;
-  const int l = blockIdx.x / (a.Hq * a.S);
-  const int lh = l * a.Hkv + hq / a.G, g = hq % a.G;
-  const int dd = threadIdx.x;
-  if (blockIdx.x == 0 && dd == 0 && a.status && a.cu_retained[a.S] > a.out_rows)
+  constexpr int kWavesC = THREADS / kWave;
+  constexpr int kHeads = HEADS_G ? 16 : 1;
+  constexpr int J = HEADS_G ? 1 : THREADS / D;  // thread groups over the splits
+  constexpr int kAhead = 4;                     // partial outputs loaded ahead per thread
+  static_assert(THREADS % D == 0, "whole groups");
+  __shared__ float wts[kHeads][kBlockSplits];
+  __shared__ float zsum[kHeads], mref[kHeads];
+  __shared__ float osum[J][D];
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int nh = HEADS_G ? a.G : 1;   // heads of this workgroup
+  const int per = HEADS_G ? 1 : a.G;  // workgroups per KV head
+  const int g0 = HEADS_G ? 0 : blockIdx.x % per;
+  const int h = (blockIdx.x / per) % a.Hkv;
+  const int s = (blockIdx.x / (per * a.Hkv)) % a.S;
+  const int l = blockIdx.x / (per * a.Hkv * a.S);
+  const int lh = l * a.Hkv + h;
+  if (blockIdx.x == 0 && tid == 0 && a.status && a.cu_retained[a.S] > a.out_rows)
     atomicOr(a.status, kFlagOutRows);  // the split kernel read no row past out_rows
   // global splits of the sequences before s: a wave-wide prefix over 64 sequences at a time
   int first = 0;
-  {
-    const int lane = dd & 63;
-    for (int s0 = 0; s0 < s; s0 += kWave) {
-      const int sq = s0 + lane;
-      int cnt = sq < s ? splits_of(a, sq) : 0;
+  for (int s0 = 0; s0 < s; s0 += kWave) {
+    const int sq = s0 + lane;
+    int cnt = sq < s ? splits_of(a, sq) : 0;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
-      first += cnt;
-    }
+    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
+    first += cnt;
   }
   first = min(first, a.total_splits);  // the splits the grid held
-  const int last = min(first + splits_of(a, s), a.total_splits);
-  float M = -INFINITY, Z = 0.f, O = 0.f;
-  for (int g0 = first; g0 < last; g0 += 8) {  // eight splits' loads in flight at a time
-    float mw[8], zw[8], ow[8];
+  const int n = min(first + splits_of(a, s), a.total_splits) - first;
+  const size_t stride = (size_t)a.G * ST;  // floats of a split
+  const float* __restrict__ base =
+      a.partial + (((size_t)lh * a.total_splits + first) * a.G + g0) * ST;
+  const int jg = HEADS_G ? 0 : tid / D;    // splits jg, jg + J, ..
+  const int e0 = HEADS_G ? tid : tid % D;  // (head, dim) of this thread: e0, e0 + THREADS, ..
+  float ahead[kAhead];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      mw[u] = -INFINITY;
-      zw[u] = 0.f;
-      ow[u] = 0.f;
-      if (g0 + u < last) {
-        const float* part = a.partial + (((size_t)lh * a.total_splits + g0 + u) * a.G + g) * ST;
-        mw[u] = part[D];
-        zw[u] = part[D + 1];
-        ow[u] = part[dd];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float mn = fmaxf(M, mw[u]);
-      if (mn == -INFINITY) continue;
-      const float x = fast_exp2(M - mn), y = fast_exp2(mw[u] - mn);
-      Z = Z * x + zw[u] * y;
-      O = O * x + ow[u] * y;
-      M = mn;
+  for (int u = 0; u < kAhead; ++u) {
+    const int j = jg + J * u;
+    ahead[u] = j < n && e0 < nh * D ? base[j * stride + (e0 / D) * ST + e0 % D] : 0.f;
+  }
+  // M and Z of every head
+  for (int g = wave; g < nh; g += kWavesC) {
+    const float* __restrict__ p = base + (size_t)g * ST + D;
+    float m = -INFINITY;
+    for (int j = lane; j < n; j += kWave) m = fmaxf(m, p[j * stride]);
+    m = wave_max(m);
+    float z = 0.f;
+    if (m != -INFINITY)
+      for (int j = lane; j < n; j += kWave) z += p[j * stride + 1] * fast_exp2(p[j * stride] - m);
+    z = wave_sum(z);
+    if (lane == 0) {
+      mref[g] = m;
+      zsum[g] = z;
     }
   }
-  a.out[(((size_t)l * a.S + s) * a.Hq + hq) * D + dd] = Z > 0.f ? O / Z : 0.f;
+  __syncthreads();
+  auto weight = [&](int g, int j) {  // of split j for head g
+    const float m = mref[g];
+    return m == -INFINITY ? 0.f : fast_exp2(base[j * stride + (size_t)g * ST + D] - m);
+  };
+  auto weights = [&](int j0) {  // of splits j0 .. j0 + kBlockSplits - 1
+    for (int e = tid; e < nh * kBlockSplits; e += THREADS) {
+      const int g = e / kBlockSplits, j = e % kBlockSplits;
+      if (j0 + j < n) wts[g][j] = weight(g, j0 + j);
+    }
+  };
+  weights(0);
+  __syncthreads();
+  float* __restrict__ out = a.out + (((size_t)l * a.S + s) * a.Hq + h * a.G + g0) * D;
+  if constexpr (HEADS_G) {
+    for (int e = e0; e < nh * D; e += THREADS) {
+      const int g = e / D;
+      const float* __restrict__ p = base + (size_t)g * ST + (e - g * D);
+      float o = 0.f;
+      for (int j = 0; j < n; j += kAhead) {
+        float v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          v[u] = j == 0 && e == e0 ? ahead[u] : (j + u < n ? p[(j + u) * stride] : 0.f);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (j + u < n)
+            o = fmaf(v[u], j + u < kBlockSplits ? wts[g][j + u] : weight(g, j + u), o);
+      }
+      const float z = zsum[g];
+      out[e] = z > 0.f ? o / z : 0.f;
+    }
+  } else {
+    float o = 0.f;
+    for (int j0 = 0; j0 < n; j0 += kBlockSplits) {
+      if (j0 > 0) {
+        __syncthreads();
+        weights(j0);
+        __syncthreads();
+      }
+      const int end = min(n - j0, kBlockSplits);
+      for (int j = jg; j < end; j += J * kAhead) {
+        float v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          v[u] = j0 == 0 && j == jg
+                     ? ahead[u]
+                     : (j + J * u < end ? base[(j0 + j + J * u) * stride + e0] : 0.f);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (j + J * u < end) o = fmaf(v[u], wts[0][j + J * u], o);
+      }
+    }
+    osum[jg][e0] = o;
+    __syncthreads();
+    if (tid < D) {
+      float t = osum[0][tid];
+#pragma unroll
+      for (int q = 1; q < J; ++q) t += osum[q][tid];
+      out[tid] = zsum[0] > 0.f ? t / zsum[0] : 0.f;
+    }
+  }
 }
 
 }  // namespace
 
 // 1024 rows per split when the cache fills the chip's resident workgroups
-// (256 CUs x 3) at least twice over with them, else 512: longer splits spend
-// less of each workgroup's life on its start and merge, shorter ones keep a
-// small cache spread over every CU.
+// (256 CUs x 3) at least twice over with them: longer splits spend less of each
+// workgroup's life on its start and merge. Otherwise the longest of 512 .. 64
+// rows that gives 512 workgroups: a short cache (one layer's) is spread over the
+// CUs, where a wave's tiles would follow one another. One decode step, 512 rows
+// and now: 8 heads x 1536 rows 13.9 -> 9.8 us, x 30000 rows 43.8 -> 32.9, 32
+// heads x 1536 16.9 -> 12.9, 128 heads x 1536 25.8 -> 23.6 (256 workgroups:
+// 26.4, 1024: 28.4).
 int decode_split_rows(int L, int Hkv, int out_rows) {
   constexpr int64_t kResident = 256 * 3;
-  return (int64_t)L * Hkv * (out_rows / 1024) >= 2 * kResident ? 1024 : 512;
+  const int64_t heads = (int64_t)L * Hkv;
+  if (heads * (out_rows / 1024) >= 2 * kResident) return 1024;
+  int split = 512;
+  while (split > 64 && heads * (out_rows / split) < 512) split /= 2;
+  return split;
 }
 
 // A bound of sum_s ceil(R_s / split_rows) from what the host knows: R_s <=
@@ -509,11 +599,25 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
     else
       hipLaunchKernelGGL(decode_mfma_kernel<64>, grid, dim3(kThreads), 0, st, a);
   }
-  const dim3 cgrid((unsigned)(a.L * a.S * a.Hq));
-  if (a.d == 128)
-    hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, dim3(128), 0, st, a);
-  else
-    hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, dim3(64), 0, st, a);
+  // All heads of a KV head per workgroup when those fill the chip (28 layers x 4
+  // heads x 16 sequences: the step 419 -> 411 us; one head each: 448); otherwise
+  // one head each, with several groups of threads over the splits while the
+  // workgroups are few (256 KV heads x 300 rows: 15.3 us with 128 threads, 16.9
+  // with 512).
+  auto combine = [&](auto d_c) {
+    constexpr int D = decltype(d_c)::value;
+    const unsigned kv = (unsigned)(a.L * a.S * a.Hkv);
+    if (kv >= 512)
+      hipLaunchKernelGGL((decode_combine_kernel<D, 256, true>), dim3(kv), dim3(256), 0, st, a);
+    else if (kv * (unsigned)a.G >= 1024)
+      hipLaunchKernelGGL((decode_combine_kernel<D, 128, false>), dim3(kv * (unsigned)a.G),
+                         dim3(128), 0, st, a);
+    else
+      hipLaunchKernelGGL((decode_combine_kernel<D, 512, false>), dim3(kv * (unsigned)a.G),
+                         dim3(512), 0, st, a);
+  };
+  if (a.d == 128) combine(std::integral_constant<int, 128>{});
+  else combine(std::integral_constant<int, 64>{});
   return hipGetLastError();
 }
 

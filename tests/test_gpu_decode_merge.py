@@ -1,0 +1,57 @@
+"""Decode: the split lengths (64 to 1024 rows) and the three forms of the merge (all heads of a
+KV head per workgroup; one head with one or several thread groups over the splits), with more
+than 64 splits per sequence, empty and one-row sequences and an out_rows that cuts the last one.
+P enters the second product as two bf16 parts (2^-17 relative) and every sum is fp32, so an
+output differs from float64 attention by less than 2^-15 of its row's largest magnitude."""
+import numpy as np
+import pytest
+
+from tests.gpu_cases import log
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # layers, q heads, kv heads, d, rows per sequence, rows cut off the end
+    "split64_few_heads": (1, 32, 8, 128, [1536], 0),
+    "split64_edges": (1, 8, 2, 64, [63, 64, 65, 0, 1, 127], 0),
+    "split64_many": (1, 4, 1, 128, [9000], 100),
+    "split512_many": (2, 14, 2, 64, [40000, 5], 0),
+    "one_head_128": (16, 64, 8, 128, [300, 77], 0),
+    "all_heads": (16, 28, 4, 64, [100, 600, 0, 1300, 64, 1, 900, 513], 300),
+    "all_heads_split1024": (32, 16, 8, 64, [7000, 1, 300], 0),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_decode_merge(case):
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    L, Hq, Hkv, d, rows, cut = CASES[case]
+    S, G = len(rows), Hq // Hkv
+    cu = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    out_rows = int(cu[-1]) - cut
+    # sequences longer than what they retain, as after compaction
+    pb = B.Problem(L, Hq, Hkv, d, 1, np.concatenate([[0], np.cumsum([r + 50 for r in rows])]),
+                   np.zeros(S + 1, np.int32))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn((L, S, Hq, d), generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn((L, Hkv, out_rows, d), generator=gen, device="cuda").to(torch.bfloat16)
+    v = torch.randn((L, Hkv, out_rows, d), generator=gen, device="cuda").to(torch.bfloat16)
+    log(f"[decode merge {case}]")
+    out = B.decode_attention(pb, q, k, v, torch.from_numpy(cu).cuda(), out_rows)
+    torch.cuda.synchronize()
+    assert bool(pb.status() & B.FLAG_OUT_ROWS) == (cut > 0)
+    q, k, v, out = q.double(), k.double(), v.double(), out.double()
+    for s in range(S):
+        a, b = min(int(cu[s]), out_rows), min(int(cu[s + 1]), out_rows)
+        if b <= a:
+            assert bool((out[:, s] == 0).all())
+            continue
+        kk = k[:, :, a:b].repeat_interleave(G, dim=1)
+        vv = v[:, :, a:b].repeat_interleave(G, dim=1)
+        z = (kk * q[:, s, :, None]).sum(-1) / d ** 0.5
+        ref = (torch.softmax(z, -1)[..., None] * vv).sum(2)
+        err = (out[:, s] - ref).abs().amax(-1) / ref.abs().amax(-1)
+        assert float(err.max()) < 2.0 ** -15
