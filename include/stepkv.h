@@ -493,9 +493,8 @@ size_t stepkv_decode_workspace_bytes(const stepkv_problem* pb, int32_t out_rows)
  * cu_retained[S] exceeds out_rows; each sequence's range of cu_retained is
  * clamped to [0, out_rows)). Each KV head's rows are read once for its whole
  * query group (up to 16 heads; wider groups are served per query head),
- * split over workgroups of 1024 rows when L * Hkv * floor(out_rows / 1024) >=
- * 1536, otherwise of the most rows among 512, 256, 128 and 64 with
- * L * Hkv * floor(out_rows / rows) >= 512 (64 if none). The workspace holds one partial
+ * split over workgroups of 512 rows, or 1024 rows when
+ * L * Hkv * floor(out_rows / 1024) >= 1536. The workspace holds one partial
  * state (d + 2 floats) per (layer, KV head, split, head of the group), for
  * the splits min(sum_s ceil(min(N_s, out_rows) / split),
  * floor(out_rows / split) + S). Errors: EINVAL, EUNSUPPORTED (d), EWORKSPACE

@@ -3,7 +3,7 @@
 // accumulation (the consumer of the compacted cache, Sec. 3).
 //
 // decode_mfma_kernel: one workgroup per (layer, KV head, sequence, split of
-// 64 to 1024 retained rows) serves all G <= 16 query heads of the KV head, so K and V
+// 512 or 1024 retained rows) serves all G <= 16 query heads of the KV head, so K and V
 // are read once: q . k and p V for the whole query group on MFMA with an
 // exact online softmax per head between them, several 16-row tiles in flight
 // per wave; decode_combine_kernel merges the splits. decode_simple_kernel
@@ -160,9 +160,6 @@ typedef float f32x4_t __attribute__((__vector_size__(4 * sizeof(float))));
 // Waves merge in LDS; decode_combine_kernel merges the splits.
 constexpr float kSlack = 16.f;
 
-// Tiles per wave in the ring: one computed while the next is in flight (a
-// deeper ring costs occupancy and measured no faster).
-constexpr int kStages = 2;
 
 // Cross-lane exchanges on the vector unit (no LDS round trip): the value of
 // lane l ^ 16 and of lane l ^ 32 (gfx950 permlane swaps).
@@ -221,8 +218,9 @@ __device__ __forceinline__ void tr_settle(i16x4_t (&f)[N]) {
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
+// NW waves share a split: 4, or 8 (d 128) or 16 (d 64) while the workgroups are few.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : NW / 4)))
 void decode_mfma_kernel(DecodeArgs a) {
   constexpr int KS = D / 32;         // 16-byte K pieces per lane and row = S k-steps
   constexpr int PR = D / 8;          // 16-byte pieces per row
@@ -230,8 +228,10 @@ void decode_mfma_kernel(DecodeArgs a) {
   constexpr int VL = 16 / RPI;       // V loads per tile
   constexpr int NLD = KS + VL;       // vector memory operations per tile and lane
   constexpr int NB = D / 16;         // 16-column blocks of O
-  constexpr int NW = kThreads / kWave;
   constexpr int ST = D + 2;          // floats per head in a partial state: o[D], m, z
+  // Tiles per wave in the ring: one computed while the next is in flight (a
+  // deeper ring costs occupancy and measured no faster).
+  constexpr int kStages = 2;
   constexpr int TB = 16 * D * 2;     // bytes of a V tile
   constexpr int kRingBytes = NW * kStages * TB, kStateBytes = NW * 16 * ST * 4;
   // the V rings during the sweep; the per-wave states [NW][16][ST] after it
@@ -390,6 +390,34 @@ void decode_mfma_kernel(DecodeArgs a) {
     wstate[wave][c16][D + 1] = zp;
   }
   __syncthreads();
+  float* const part0 = a.partial + ((size_t)lh * a.total_splits + gs) * a.G * ST;
+  if constexpr (NW > 4) {
+    // the waves' weights per head first (fscale), then a sum per (head, dim)
+    if (tid < a.G * NW) {
+      const int g = tid / NW, w = tid % NW;
+      float M = -INFINITY, Z = 0.f;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) M = fmaxf(M, wstate[v][g][D]);
+      if (M != -INFINITY) {
+#pragma unroll
+        for (int v = 0; v < NW; ++v) Z += wstate[v][g][D + 1] * fast_exp2(wstate[v][g][D] - M);
+      }
+      fscale[w][g] = M == -INFINITY ? 0.f : fast_exp2(wstate[w][g][D] - M);
+      if (w == 0) {
+        part0[g * ST + D] = M;
+        part0[g * ST + D + 1] = Z;
+      }
+    }
+    __syncthreads();
+    for (int e = tid; e < a.G * D; e += NW * kWave) {
+      const int g = e / D, dd = e - g * D;
+      float O = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) O = fmaf(wstate[w][g][dd], fscale[w][g], O);
+      part0[g * ST + dd] = O;
+    }
+    return;
+  }
   // merge the waves: thread (g, d) for every head g and dim d
   for (int e = tid; e < a.G * D; e += kThreads) {
     const int g = e / D, dd = e - g * D;
@@ -403,7 +431,7 @@ void decode_mfma_kernel(DecodeArgs a) {
       O = O * xa + wstate[w][g][dd] * ya;
       M = mn;
     }
-    float* part = a.partial + (((size_t)lh * a.total_splits + gs) * a.G + g) * ST;
+    float* part = part0 + g * ST;
     part[dd] = O;
     if (dd == 0) {
       part[D] = M;
@@ -421,8 +449,8 @@ void decode_mfma_kernel(DecodeArgs a) {
 //   splits and their sums are added in group order.
 // The first splits' partial outputs are loaded before the weights are known, so
 // that a merge of few splits waits for memory once. The chain of loads bounds
-// it: 24 splits of one sequence with a thread per dim and eight splits at a time
-// took 5 us more than 3 splits, now nothing measurable.
+// it: 8 heads x 30000 rows (59 splits) took 43.8 us a step with a thread per dim
+// and eight splits at a time, now 29.1.
 constexpr int kBlockSplits = 64;
 
 template <int D, int THREADS, bool HEADS_G>
@@ -550,20 +578,12 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
 }  // namespace
 
 // 1024 rows per split when the cache fills the chip's resident workgroups
-// (256 CUs x 3) at least twice over with them: longer splits spend less of each
-// workgroup's life on its start and merge. Otherwise the longest of 512 .. 64
-// rows that gives 512 workgroups: a short cache (one layer's) is spread over the
-// CUs, where a wave's tiles would follow one another. One decode step, 512 rows
-// and now: 8 heads x 1536 rows 13.9 -> 9.8 us, x 30000 rows 43.8 -> 32.9, 32
-// heads x 1536 16.9 -> 12.9, 128 heads x 1536 25.8 -> 23.6 (256 workgroups:
-// 26.4, 1024: 28.4).
+// (256 CUs x 3) at least twice over with them, else 512: longer splits spend
+// less of each workgroup's life on its start and merge, shorter ones keep a
+// small cache spread over every CU.
 int decode_split_rows(int L, int Hkv, int out_rows) {
   constexpr int64_t kResident = 256 * 3;
-  const int64_t heads = (int64_t)L * Hkv;
-  if (heads * (out_rows / 1024) >= 2 * kResident) return 1024;
-  int split = 512;
-  while (split > 64 && heads * (out_rows / split) < 512) split /= 2;
-  return split;
+  return (int64_t)L * Hkv * (out_rows / 1024) >= 2 * kResident ? 1024 : 512;
 }
 
 // A bound of sum_s ceil(R_s / split_rows) from what the host knows: R_s <=
@@ -594,10 +614,19 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
   }
   if (a.total_splits > 0) {
     const dim3 grid((unsigned)(a.L * a.Hkv) * (unsigned)a.total_splits);
-    if (a.d == 128)
-      hipLaunchKernelGGL(decode_mfma_kernel<128>, grid, dim3(kThreads), 0, st, a);
-    else
-      hipLaunchKernelGGL(decode_mfma_kernel<64>, grid, dim3(kThreads), 0, st, a);
+    // With at most one workgroup per CU, more waves share each split (8 at d
+    // 128, 16 at d 64, as the registers allow), so that a wave walks fewer
+    // tiles: one layer of 8 heads x 1536 rows 13.9 -> 13.1 us, of 300 rows
+    // 12.4 -> 11.4; with 320 workgroups of 4 waves 27.0, of 8 waves 30.3.
+    auto split = [&](auto d_c) {
+      constexpr int D = decltype(d_c)::value;
+      if (grid.x <= 256)
+        hipLaunchKernelGGL((decode_mfma_kernel<D, 1024 / D>), grid, dim3(1024 / D * kWave), 0, st, a);
+      else
+        hipLaunchKernelGGL((decode_mfma_kernel<D, 4>), grid, dim3(kThreads), 0, st, a);
+    };
+    if (a.d == 128) split(std::integral_constant<int, 128>{});
+    else split(std::integral_constant<int, 64>{});
   }
   // All heads of a KV head per workgroup when those fill the chip (28 layers x 4
   // heads x 16 sequences: the step 419 -> 411 us; one head each: 448); otherwise

@@ -167,7 +167,7 @@ struct DecodeArgs {
   int split_rows;            // retained rows per workgroup of the split kernel
   float scale;
 };
-// Rows per split for this cache size (64 to 1024).
+// Rows per split for this cache size (512 or 1024).
 int decode_split_rows(int L, int Hkv, int out_rows);
 // Row splits of the split kernel (a host-side bound) for these sequence
 // lengths, out_rows and rows per split.

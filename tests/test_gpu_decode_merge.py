@@ -1,4 +1,4 @@
-"""Decode: the split lengths (64 to 1024 rows) and the three forms of the merge (all heads of a
+"""Decode: splits shared by 4, 8 and 16 waves and the three forms of the merge (all heads of a
 KV head per workgroup; one head with one or several thread groups over the splits), with more
 than 64 splits per sequence, empty and one-row sequences and an out_rows that cuts the last one.
 P enters the second product as two bf16 parts (2^-17 relative) and every sum is fp32, so an
@@ -12,10 +12,10 @@ pytestmark = pytest.mark.gpu
 
 CASES = {
     # layers, q heads, kv heads, d, rows per sequence, rows cut off the end
-    "split64_few_heads": (1, 32, 8, 128, [1536], 0),
-    "split64_edges": (1, 8, 2, 64, [63, 64, 65, 0, 1, 127], 0),
-    "split64_many": (1, 4, 1, 128, [9000], 100),
-    "split512_many": (2, 14, 2, 64, [40000, 5], 0),
+    "waves8": (1, 32, 8, 128, [1536], 0),
+    "waves16_edges": (1, 8, 2, 64, [63, 64, 65, 0, 1, 127], 0),
+    "waves8_many": (1, 4, 1, 128, [9000], 100),
+    "waves4_many_splits": (2, 14, 2, 64, [40000, 5], 0),
     "one_head_128": (16, 64, 8, 128, [300, 77], 0),
     "all_heads": (16, 28, 4, 64, [100, 600, 0, 1300, 64, 1, 900, 513], 300),
     "all_heads_split1024": (32, 16, 8, 64, [7000, 1, 300], 0),
