@@ -313,11 +313,10 @@ int max_steps_per_seq(const stepkv_problem* pb) {
 
 // Saliency sweeps into `sal` (or the row LSE into lse_out, or from lse_in),
 // using workspace regions below layout().sal.
-int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
-                 const void* k, float* sal, uint8_t* ws, hipStream_t st,
+int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const SaliencyPlan& plan,
+                 const void* q_win, const void* k, float* sal, uint8_t* ws, hipStream_t st,
                  SaliencyMode mode = SaliencyMode::kBoth, const float* lse_in = nullptr,
-                 float* lse_out = nullptr, bool may_keep = true) {
-  const SaliencyPlan plan = plan_saliency(pb, may_keep);
+                 float* lse_out = nullptr) {
   const WsLayout w = layout(pb, plan);
   const int d = pb->head_dim;
   SaliencyArgs sa;
@@ -481,11 +480,11 @@ struct SharedLayout {
                                       // chunk maxima of the multi-workgroup priority
 };
 
-SharedLayout shared_layout(const stepkv_problem* pb, int n) {
-  const stepkv_problem sub = last_layers_view(pb, n);
+SharedLayout shared_layout(const stepkv_problem* pb, int n, const stepkv_problem& sub,
+                           const SaliencyPlan& plan) {
   const size_t ntot = (size_t)pb->cu_seqlens_host[pb->num_seqs];
   SharedLayout w;
-  w.heads = layout(&sub, plan_saliency(&sub)).sal;  // after the sweep workspace
+  w.heads = layout(&sub, plan).sal;  // after the sweep workspace
   w.shared = align_up(w.heads + sizeof(float) * n * pb->num_kv_heads * ntot);
   w.cmax = align_up(w.shared + sizeof(float) * ntot);
   w.total = align_up(w.cmax + sizeof(float) * shared_chunks(pb->cu_seqlens_host, pb->num_seqs));
@@ -498,11 +497,11 @@ struct CompressLayout {
   size_t scores, idx, total;
 };
 
-CompressLayout compress_layout(const stepkv_problem* pb) {
+CompressLayout compress_layout(const stepkv_problem* pb, const SaliencyPlan& plan) {
   const size_t entries = (size_t)pb->num_layers * pb->num_kv_heads *
                          (size_t)pb->cu_seqlens_host[pb->num_seqs];
   CompressLayout c;
-  c.scores = layout(pb, plan_saliency(pb)).total;
+  c.scores = layout(pb, plan).total;
   c.idx = align_up(c.scores + sizeof(float) * entries);
   c.total = align_up(c.idx + sizeof(int32_t) * entries);
   return c;
@@ -519,10 +518,11 @@ int stepkv_saliency(const stepkv_problem* pb, const stepkv_params* prm, const vo
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !saliency) return STEPKV_EINVAL;
-  const WsLayout w = layout(pb, plan_saliency(pb));
+  const SaliencyPlan plan = plan_saliency(pb);
+  const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
-  return run_saliency(pb, prm, q_win, k, saliency, static_cast<uint8_t*>(workspace),
+  return run_saliency(pb, prm, plan, q_win, k, saliency, static_cast<uint8_t*>(workspace),
                       static_cast<hipStream_t>(stream));
 }
 
@@ -553,13 +553,14 @@ int stepkv_score(const stepkv_problem* pb, const stepkv_params* prm, const void*
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  const WsLayout w = layout(pb, plan_saliency(pb));
+  const SaliencyPlan plan = plan_saliency(pb);
+  const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   float* sal = saliency ? saliency : reinterpret_cast<float*>(ws + w.sal);
-  rc = run_saliency(pb, prm, q_win, k, sal, ws, st);
+  rc = run_saliency(pb, prm, plan, q_win, k, sal, ws, st);
   if (rc != STEPKV_OK) return rc;
   return run_priority(pb, prm, sal, step_ids, protected_mask, step_utility, scores, step_stats,
                       st);
@@ -579,14 +580,14 @@ int stepkv_score_noalloc(const stepkv_problem* pb, const stepkv_params* prm, con
   if (rc != STEPKV_OK) return rc;
   // the sweeps' workspace (everything but the saliency buffer, which the caller
   // passes), with the logits of few window rows where they fit
-  const bool may_keep = layout(pb, plan_saliency(pb)).sal <= kStaticScratchBytes;
-  if (layout(pb, plan_saliency(pb, may_keep)).sal > kStaticScratchBytes) return STEPKV_ESCRATCH;
+  SaliencyPlan plan = plan_saliency(pb);
+  if (plan.few && layout(pb, plan).sal > kStaticScratchBytes) plan = plan_saliency(pb, false);
+  if (layout(pb, plan).sal > kStaticScratchBytes) return STEPKV_ESCRATCH;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
   void* ws = nullptr;
   if (static_scratch(&ws) != hipSuccess || !ws) return STEPKV_EHIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  rc = run_saliency(pb, prm, q_win, k, saliency, static_cast<uint8_t*>(ws), st,
-                    SaliencyMode::kBoth, nullptr, nullptr, may_keep);
+  rc = run_saliency(pb, prm, plan, q_win, k, saliency, static_cast<uint8_t*>(ws), st);
   if (rc != STEPKV_OK) return rc;
   return run_priority(pb, prm, saliency, step_ids, protected_mask, step_utility, scores,
                       step_stats, st);
@@ -599,10 +600,11 @@ int stepkv_window_lse(const stepkv_problem* pb, const stepkv_params* prm, const 
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !lse_win) return STEPKV_EINVAL;
-  const WsLayout w = layout(pb, plan_saliency(pb));
+  const SaliencyPlan plan = plan_saliency(pb);
+  const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   // runs even without keys: every row then sees none and gets -inf
-  return run_saliency(pb, prm, q_win, k, nullptr, static_cast<uint8_t*>(workspace),
+  return run_saliency(pb, prm, plan, q_win, k, nullptr, static_cast<uint8_t*>(workspace),
                       static_cast<hipStream_t>(stream), SaliencyMode::kLseOnly, nullptr, lse_win);
 }
 
@@ -613,10 +615,11 @@ int stepkv_saliency_from_lse(const stepkv_problem* pb, const stepkv_params* prm,
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !lse_win || !saliency) return STEPKV_EINVAL;
-  const WsLayout w = layout(pb, plan_saliency(pb));
+  const SaliencyPlan plan = plan_saliency(pb);
+  const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
-  return run_saliency(pb, prm, q_win, k, saliency, static_cast<uint8_t*>(workspace),
+  return run_saliency(pb, prm, plan, q_win, k, saliency, static_cast<uint8_t*>(workspace),
                       static_cast<hipStream_t>(stream), SaliencyMode::kFromLse, lse_win);
 }
 
@@ -632,13 +635,14 @@ int stepkv_score_from_lse(const stepkv_problem* pb, const stepkv_params* prm, co
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  const WsLayout w = layout(pb, plan_saliency(pb));
+  const SaliencyPlan plan = plan_saliency(pb);
+  const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   float* sal = saliency ? saliency : reinterpret_cast<float*>(ws + w.sal);
-  rc = run_saliency(pb, prm, q_win, k, sal, ws, st, SaliencyMode::kFromLse, lse_win);
+  rc = run_saliency(pb, prm, plan, q_win, k, sal, ws, st, SaliencyMode::kFromLse, lse_win);
   if (rc != STEPKV_OK) return rc;
   return run_priority(pb, prm, sal, step_ids, protected_mask, step_utility, scores, step_stats,
                       st);
@@ -646,7 +650,9 @@ int stepkv_score_from_lse(const stepkv_problem* pb, const stepkv_params* prm, co
 
 size_t stepkv_score_shared_workspace_bytes(const stepkv_problem* pb, int32_t last_layers) {
   if (check_problem(pb) != STEPKV_OK || last_layers < 1) return 0;
-  return shared_layout(pb, shared_layers(pb, last_layers)).total;
+  const int n = shared_layers(pb, last_layers);
+  const stepkv_problem sub = last_layers_view(pb, n);
+  return shared_layout(pb, n, sub, plan_saliency(&sub)).total;
 }
 
 int stepkv_score_shared(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
@@ -663,7 +669,9 @@ int stepkv_score_shared(const stepkv_problem* pb, const stepkv_params* prm, cons
                            saliency, 1);
   if (rc != STEPKV_OK) return rc;
   const int n = shared_layers(pb, last_layers);
-  const SharedLayout w = shared_layout(pb, n);
+  const stepkv_problem sub = last_layers_view(pb, n);
+  const SaliencyPlan plan = plan_saliency(&sub);
+  const SharedLayout w = shared_layout(pb, n, sub, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   const int ntot = pb->cu_seqlens_host[pb->num_seqs];
   if (ntot == 0) return STEPKV_OK;
@@ -676,9 +684,8 @@ int stepkv_score_shared(const stepkv_problem* pb, const stepkv_params* prm, cons
   const uint16_t* kk =
       static_cast<const uint16_t*>(k) + first * pb->num_kv_heads * (size_t)ntot * pb->head_dim;
   const float* lse = lse_win ? lse_win + first * q_layer : nullptr;
-  const stepkv_problem sub = last_layers_view(pb, n);
   float* heads = reinterpret_cast<float*>(ws + w.heads);
-  rc = run_saliency(&sub, prm, q, kk, heads, ws, st,
+  rc = run_saliency(&sub, prm, plan, q, kk, heads, ws, st,
                     lse ? SaliencyMode::kFromLse : SaliencyMode::kBoth, lse);
   if (rc != STEPKV_OK) return rc;
   float* sal = saliency ? saliency : reinterpret_cast<float*>(ws + w.shared);
@@ -787,7 +794,7 @@ int stepkv_compact(const stepkv_problem* pb, const void* k, const void* v, const
 
 size_t stepkv_compress_workspace_bytes(const stepkv_problem* pb) {
   if (check_problem(pb) != STEPKV_OK) return 0;
-  return compress_layout(pb).total;
+  return compress_layout(pb, plan_saliency(pb)).total;
 }
 
 int stepkv_compress(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
@@ -805,15 +812,16 @@ int stepkv_compress(const stepkv_problem* pb, const stepkv_params* prm, const vo
   if (out_rows > 0 && (!k_out || !v_out)) return STEPKV_EINVAL;  // NULL outputs hold 0 rows
   if (!step_utility && pb->cu_steps_host[pb->num_seqs] > 0) return STEPKV_EINVAL;
   if (!budgets && budget < 1) return STEPKV_EINVAL;
-  const CompressLayout cl = compress_layout(pb);
+  const SaliencyPlan plan = plan_saliency(pb);
+  const CompressLayout cl = compress_layout(pb, plan);
   if (!workspace || ws_bytes < cl.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   float* P = scores ? scores : reinterpret_cast<float*>(ws + cl.scores);
   int32_t* I = idx ? idx : reinterpret_cast<int32_t*>(ws + cl.idx);
   if (pb->cu_seqlens_host[pb->num_seqs] > 0) {
-    float* sal = reinterpret_cast<float*>(ws + layout(pb, plan_saliency(pb)).sal);
-    rc = run_saliency(pb, prm, q_win, k, sal, ws, st,
+    float* sal = reinterpret_cast<float*>(ws + layout(pb, plan).sal);
+    rc = run_saliency(pb, prm, plan, q_win, k, sal, ws, st,
                       lse_win ? SaliencyMode::kFromLse : SaliencyMode::kBoth, lse_win);
     if (rc != STEPKV_OK) return rc;
     const FuseArgs fa = fuse_args(pb, prm, sal, step_ids, protected_mask, step_utility, P, nullptr);
