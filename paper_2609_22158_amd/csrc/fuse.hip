@@ -1,8 +1,9 @@
 // Pooling, normalisation and step-utility fusion (Sec. 5.2, eq. token-priority).
-// Without step statistics, and with more (sequence, head) rows than CUs or
-// more than 4096 steps in a sequence, each row is spread over workgroups of
-// 2048 positions (prio_chunk_*). Otherwise one workgroup per (sequence,
-// head). Both compute
+// Without step statistics, and with more (sequence, head) rows than CUs, more
+// than 4096 steps or more than 32768 positions in a sequence, each row is spread
+// over workgroups of 2048 positions (prio_chunk_*). Otherwise one workgroup per
+// (sequence, head). stepkv_compress ranks rows of up to 32768 positions in
+// rank_kernel (select.hip) instead. All compute
 //   U_i  = sum_{|j-i| <= half} A_j [j prunable]     (k * T_i; zero padded)
 //   Th_i = U_i / max_{prunable} U                   (the 1/k cancels)
 //   P_i  = alpha * Th_i + beta * S[step_ids[i]]     (prunable; -inf if protected)
