@@ -146,12 +146,21 @@ SaliencyPlan plan_saliency(const stepkv_problem* pb, bool may_keep = true) {
   // are enough chunks for the row-LSE items to run a round ahead.
   const int64_t k_bytes = lh * (int64_t)pb->cu_seqlens_host[pb->num_seqs] * 2 * pb->head_dim;
   p.fused_pays = k_bytes > kFusedReuseBytes && lh * p.fused_total_chunks >= 2 * kSalSlots;
-  // Few rows: a chunk (a multiple of 64 keys, a tile per wave) for about twelve
-  // workgroups per compute unit, six of which are resident.
+  // Few rows: a chunk (a multiple of 64 keys, a tile per wave) for one workgroup
+  // per compute unit, of 128 keys at least and 1024 at most (three workgroups of
+  // d 128 are resident on a compute unit, six of d 64), but at most 512 chunks in
+  // a sequence: every workgroup of the sums reads all partials of its (sequence,
+  // head), so their cost grows with the square of the chunk count. One head of
+  // 524288 keys, R 4: 40 us with chunks of 1024 (two sweeps: 57), 81 of 256, 214
+  // of 128; two heads of 131071, R 8: 22, 32, 50 (two sweeps: 35); eight heads of
+  // 32768, R 4: 19, 23, 31 (32); three layers of those 44, 53, 76 (73); eight
+  // heads of 8192 13.5 from 128 to 512 keys and 16.2 with 1024.
   p.few = may_keep && few_rows(p.R);
   const int64_t ntot = pb->cu_seqlens_host[pb->num_seqs];
-  p.few_chunk = (int)std::min<int64_t>(
-      1024, std::max<int64_t>(128, (lh * ntot / (12 * 256) + 63) / 64 * 64));
+  auto whole_tiles = [](int64_t keys) { return (keys + 63) / 64 * 64; };
+  p.few_chunk = (int)std::max(
+      std::min<int64_t>(1024, std::max<int64_t>(128, whole_tiles(lh * ntot / 256))),
+      whole_tiles((max_seqlen(pb) + 511) / 512));
   p.few_total_chunks = (int)chunks_for(p.few_chunk);
   p.few_slots = (ntot + 15) / 16 * 16 + 16 * (int64_t)pb->num_seqs;
   return p;

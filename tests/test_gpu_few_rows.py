@@ -71,3 +71,34 @@ def test_few_rows_workspace_stays_in_bounds():
     B.saliency(pb, q, k, B.Params(), workspace=ws[:need])
     torch.cuda.synchronize()
     assert bool((ws[need:] == 0xA5).all())
+
+
+def test_long_sequence_is_not_slower_than_two_sweeps():
+    """One head of 524288 keys. Every workgroup of the sums reads all partials of its sequence,
+    so short chunks cost the square of their number: 125 us with chunks of 192 keys, 57 with two
+    sweeps, 40 with chunks of 1024."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    n = 524288
+    pb = B.Problem(1, 4, 1, 128, 1, np.array([0, n]), np.zeros(2, np.int32))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            for s in ((1, 1, 1, 4, 128), (1, 1, n, 128)))
+    ws = torch.empty(pb.saliency_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    out = {s: torch.empty((1, 1, n), device="cuda") for s in (0, 1)}
+
+    def passes(sched):  # ms of 20 passes
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            B.saliency(pb, q, k, B.Params(saliency_schedule=sched), workspace=ws, out=out[sched])
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b)
+
+    log("[few rows long]")
+    t = {s: sorted(passes(s) for _ in range(5))[2] for s in (0, 1)}
+    torch.testing.assert_close(out[0], out[1], rtol=1.1e-5, atol=1e-12)
+    assert t[0] < 1.3 * t[1], t
