@@ -41,7 +41,31 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for<B + 1, E>(f);
   }
 }
-constexpr int kFewRows = 8;     // most rows taken
+
+// The fragments at addr[ks] + OFF in LDS. The reads and their wait are one
+// block: the compiler takes an asm's outputs as written when it ends. (In
+// assembly, so that no wait for the whole K ring is put in front of them.)
+template <int OFF>
+__device__ __forceinline__ void read_fragments(const uint32_t (&addr)[4], bf16x8_t (&f)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %4 offset:%8\n\tds_read_b128 %1, %5 offset:%8\n\t"
+      "ds_read_b128 %2, %6 offset:%8\n\tds_read_b128 %3, %7 offset:%8\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
+      : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "n"(OFF)
+      : "memory");
+}
+template <int OFF>
+__device__ __forceinline__ void read_fragments(const uint32_t (&addr)[2], bf16x8_t (&f)[2]) {
+  asm volatile(
+      "ds_read_b128 %0, %2 offset:%4\n\tds_read_b128 %1, %3 offset:%4\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(f[0]), "=&v"(f[1])
+      : "v"(addr[0]), "v"(addr[1]), "n"(OFF)
+      : "memory");
+}
+
+constexpr int kFewRows = 8;      // most rows taken
 constexpr int kMaxFewRows = 16;  // rows of the MFMA tile and of a partial
 
 // First logit slot of sequence s: whole tiles that no other sequence's reach.
@@ -149,11 +173,7 @@ __global__ __launch_bounds__(kThreads) void row_logits_kernel(SaliencyArgs a) {
       // stores of logits count too: this waits for a little more than the tile
       wait_tiles<NL, kRing - 1>(ahead);
       bf16x8_t f[KS];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f[ks]) : "v"(fa[ks]), "n"(u * TB) : "memory");
-      if constexpr (KS == 4) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
-      else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]));
+      read_fragments<u * TB>(fa, f);
       compute(wave + 4 * i, f);
     });
   }

@@ -1,8 +1,12 @@
 """Saliency of at most 8 window rows (K read once, logits kept): row counts 1 to 8 on both
-quads, sequences around the 16-key tiles and the chunks, more sequences than the launch
-arguments hold, the causal tail and both head dims, against the oracle and against the
-two-sweep schedule. Both sides compute exp2(c z - lse) in fp32 with |c z - lse| below 64 here,
-so they differ by a few roundings of that exponent: 64 * 2^-24 * ln 2 * 4 = 1.1e-5 at most."""
+quads, sequences around the 16-key tiles and the chunks, chunks of up to 1024 keys (K rings past
+their first fill), more sequences than the launch arguments hold, the causal tail, both head
+dims, NaN and infinite keys, against the oracle, float64 and the two-sweep schedule. Both
+schedules compute exp2(c z - lse) in fp32 with |c z - lse| below 64 here, so they differ by a few
+roundings of that exponent: 64 * 2^-24 * ln 2 * 4 = 1.1e-5 at most. Against float64, a logit is
+the fp32 sum of up to 128 exact products whose magnitudes sum to less than 12 after scaling
+(unit normals: 128 * 0.64 / sqrt(128) = 7.2 on average), off by less than
+128 * 2^-24 * 12 = 9.2e-5, and a row's LSE by no more: 2e-4 with the roundings above."""
 import numpy as np
 import pytest
 
@@ -54,6 +58,65 @@ def test_few_rows_saliency(shape, causal):
                 ref = O.window_saliency(rows, O.decode_bf16(w.k[l, h, a:b]),
                                         1.0 / np.sqrt(w.head_dim), vis)
                 np.testing.assert_allclose(A[l, h, a:b], ref, rtol=SCORE_RTOL, atol=1e-9)
+
+
+RINGS = {
+    # layers, KV heads, head dim, G, window, sequence lengths; the chunk these make
+    "r1_d128_640": (4, 8, 128, 1, 1, [4100, 900]),
+    "r3_d64_576": (3, 6, 64, 1, 3, [5000, 17, 3001]),
+    "r5_d128_768": (2, 4, 128, 1, 5, [24333]),
+    "r6_d64_1024": (8, 4, 64, 3, 2, [8200]),
+    "r8_d128_1024": (16, 2, 128, 4, 2, [8207, 1, 0, 1030]),
+}
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("case", list(RINGS))
+def test_few_rows_long_chunks(case, causal):
+    """Chunks of up to 16 tiles per wave, odd last chunks among them."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    L, H, d, G, W, lens = RINGS[case]
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    pb = B.Problem(L, H * G, H, d, W, cu, np.zeros(len(lens) + 1, np.int32))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            for s in ((L, len(lens), W, H * G, d), (L, H, int(cu[-1]), d)))
+    log(f"[few rows {case} causal={causal}]")
+    A = B.saliency(pb, q, k, B.Params(causal_tail=causal)).double()
+    for s, n in enumerate(lens):
+        a = int(cu[s])
+        # rows (w, g) of every head: [L][H][W * G][d]
+        rows = q[:, s].view(L, W, H, G, d).permute(0, 2, 1, 3, 4).reshape(L, H, W * G, d).double()
+        z = (rows[:, :, :, None] * k[:, :, None, a:a + n].double()).sum(-1) / d ** 0.5
+        if causal:
+            last = n - W + torch.arange(W, device="cuda").repeat_interleave(G)
+            z = z.masked_fill(torch.arange(n, device="cuda") > last[:, None], float("-inf"))
+        p = torch.softmax(z, -1).nan_to_num(0.0)  # a row that sees no key adds nothing
+        torch.testing.assert_close(A[:, :, a:a + n], p.sum(2), rtol=2e-4, atol=1e-30)
+
+
+@pytest.mark.parametrize("bad", ["nan", "inf", "-inf"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_few_rows_non_finite_keys(d, bad):
+    """A key with a NaN or an infinity leaves NaN and finite values where two sweeps leave them."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    lens = [1000, 17, 129]
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    pb = B.Problem(1, 4, 1, d, 2, cu, np.zeros(len(lens) + 1, np.int32))
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            for s in ((1, len(lens), 2, 4, d), (1, 1, int(cu[-1]), d)))
+    for at in (333, 1016, 1100):  # inside, the last key of a sequence, inside
+        k[0, 0, at, 5] = float(bad)
+    out = [B.saliency(pb, q, k, B.Params(saliency_schedule=s)) for s in (0, 1)]
+    assert bool(torch.isnan(out[0]).any())
+    torch.testing.assert_close(out[0], out[1], rtol=1.1e-5, atol=1e-12, equal_nan=True)
 
 
 def test_few_rows_workspace_stays_in_bounds():
