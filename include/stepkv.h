@@ -150,8 +150,8 @@ typedef struct stepkv_params {
    * exceeds 192 MiB and there are at least twice as many chunks as resident
    * workgroups, otherwise one launch per sweep; 1 = one launch per sweep;
    * 2 = one launch. With at most 8 window rows (W * G), 0 reads K once and
-   * keeps its logits in the workspace. Calls given the row LSEs run one sweep
-   * either way. */
+   * keeps its logits in the workspace, if that has room for them. Calls given
+   * the row LSEs run one sweep either way. */
   int32_t saliency_schedule;
 } stepkv_params;
 
@@ -264,9 +264,17 @@ int stepkv_text_cues(const char* text, int64_t text_len, uint64_t* cues, int32_t
 
 /* ---------------------------------------------------------------- device passes */
 /* Bytes of device workspace stepkv_score needs for this problem (0 when the
- * problem is invalid); with at most 8 window rows it holds 16 or 32 bytes of
- * logits per token, layer and KV head. The workspace needs no initialisation and is
- * scratch between calls; 256-byte alignment is required. */
+ * problem is invalid). The workspace needs no initialisation and is scratch
+ * between calls; 256-byte alignment is required.
+ * With at most 8 window rows the sizes include room for the logits of some or
+ * all heads (16 or 32 bytes per token): up to 272 MiB beside the saliency buffer
+ * for a whole pass (this function, stepkv_compress_workspace_bytes,
+ * stepkv_score_shared_workspace_bytes), up to STEPKV_STATIC_SCRATCH_BYTES in
+ * all for stepkv_saliency. A call takes less: with the smaller of the two rooms
+ * it works through the heads in more groups (the same results), and with no
+ * room for logits it reads K twice (the same to rounding). Calls that are given
+ * row LSEs, return them or force a schedule need none of it. EWORKSPACE is
+ * returned for less than the size without logits. */
 size_t stepkv_score_workspace_bytes(const stepkv_problem* pb);
 
 /* Bytes of device workspace stepkv_saliency needs (0 when invalid); never
@@ -344,8 +352,9 @@ int stepkv_priority(const stepkv_problem* pb, const stepkv_params* prm, const fl
  * EUNSUPPORTED for d not in {64,128}, W*G > STEPKV_MAX_WINDOW_ROWS or a
  * pool window above STEPKV_MAX_POOL_KERNEL (or more than
  * STEPKV_MAX_STEPS_STATS steps in one sequence when step_stats is requested),
- * EWORKSPACE when ws_bytes < stepkv_score_workspace_bytes(pb), EHIP on launch
- * failure. Results are deterministic (fixed reduction orders). */
+ * EWORKSPACE when ws_bytes < stepkv_score_workspace_bytes(pb) (of few window
+ * rows: less the logits), EHIP on launch failure. Results are deterministic
+ * (fixed reduction orders). */
 int stepkv_score(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
                  const void* k, const int32_t* step_ids, const uint8_t* protected_mask,
                  const float* step_utility, float* scores, float* saliency,
@@ -360,10 +369,8 @@ int stepkv_score(const stepkv_problem* pb, const stepkv_params* prm, const void*
  * (fp32 [L][Hkv][Ntot], the A buffer the sweeps write) is required here.
  * Same arguments, results and errors as stepkv_score otherwise, plus
  * STEPKV_ESCRATCH when the problem needs more than the buffer
- * (stepkv_saliency_workspace_bytes(pb) > STEPKV_STATIC_SCRATCH_BYTES, the
- * logits of few window rows left out: where those do not fit, K is read twice
- * and the results agree with stepkv_score to rounding), found before anything
- * is launched. The first call on a device looks the buffer's
+ * (stepkv_saliency_workspace_bytes(pb) > STEPKV_STATIC_SCRATCH_BYTES), found
+ * before anything is launched. The first call on a device looks the buffer's
  * address up (EHIP if that fails). Every call on one GPU shares its buffer,
  * which keeps the last call's contents (no part of it needs to start at
  * zero): calls that overlap on one GPU, on different streams or threads,

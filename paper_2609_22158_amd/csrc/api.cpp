@@ -74,17 +74,55 @@ struct SaliencyPlan {
   // both sweeps in one launch: chunk, chunk count and row-LSE lead (items)
   int fused_chunk, fused_total_chunks, fused_lag;
   bool fused_pays;  // the schedule chosen per problem (stepkv_params.saliency_schedule 0)
-  // few window rows: K read once with its logits kept (schedule 0 only)
+  // few window rows: K read once with its logits kept (schedule 0 only),
+  // few_heads (layer, KV head) pairs at a time
   bool few;
-  int few_chunk, few_total_chunks;
+  int few_chunk, few_total_chunks, few_heads;
   int64_t few_slots;  // logit slots per head
 };
+
+size_t few_head_bytes(const SaliencyPlan& p) {
+  return sizeof(float) * p.few_slots * 4 * few_rows_quads(p.R);
+}
+
+struct WsLayout {
+  size_t partial, lse, cnt, logits, sal, total;
+};
+
+WsLayout layout(const stepkv_problem* pb, const SaliencyPlan& p) {
+  const size_t lh = (size_t)pb->num_layers * pb->num_kv_heads;
+  const size_t ntot = (size_t)pb->cu_seqlens_host[pb->num_seqs];
+  WsLayout w;
+  size_t off = 0;
+  w.partial = off;  // sized for the longest chunk list of the plans
+  off = align_up(off + sizeof(float) * 2 * lh *
+                           std::max((size_t)std::max(p.total_chunks, p.fused_total_chunks) * p.rows_pad,
+                                    p.few ? (size_t)p.few_total_chunks * 16 : 0));
+  w.lse = off;
+  off = align_up(off + sizeof(float) * pb->num_seqs * lh * p.rows_pad);
+  w.cnt = off;  // per (sequence, head) counters of the one-launch sweeps
+  off = align_up(off + sizeof(int32_t) * pb->num_seqs * lh);
+  w.logits = off;
+  if (p.few) off = align_up(off + few_head_bytes(p) * p.few_heads);
+  w.sal = off;
+  off = align_up(off + sizeof(float) * lh * ntot);
+  w.total = off;
+  return w;
+}
 
 // Window rows per pair of sweeps (the MFMA tiling holds at most 256).
 constexpr int kRowGroup = 256;
 
-// may_keep: whether the workspace may hold the logits of few window rows.
-SaliencyPlan plan_saliency(const stepkv_problem* pb, bool may_keep = true) {
+// Few window rows work through the heads in groups whose logits fit a room (the
+// whole workspace of the sweeps), with the same results for every room. The
+// static scratch's room is the size that stepkv_saliency asks for. The wide room
+// is worth its memory where it takes all heads at once (saliency of the 32-layer
+// 32k cache: one group 410 us at R 4 and 458 at R 8, two and three in the static
+// room 420 and 469); past the 256 MB Infinity Cache more groups are faster (four
+// times the keys, R 4: 1740 us in one group, 1676 in five).
+constexpr size_t kWideRoomBytes = size_t(272) << 20;
+
+SaliencyPlan plan_saliency(const stepkv_problem* pb, size_t room) {
   SaliencyPlan p;
   p.R = window_rows(pb);
   p.rows_pad = saliency_rows_pad(std::min(p.R, kRowGroup));  // the first (widest) group
@@ -155,40 +193,26 @@ SaliencyPlan plan_saliency(const stepkv_problem* pb, bool may_keep = true) {
   // of 128; two heads of 131071, R 8: 22, 32, 50 (two sweeps: 35); eight heads of
   // 32768, R 4: 19, 23, 31 (32); three layers of those 44, 53, 76 (73); eight
   // heads of 8192 13.5 from 128 to 512 keys and 16.2 with 1024.
-  p.few = may_keep && few_rows(p.R);
+  p.few = few_rows(p.R);
   const int64_t ntot = pb->cu_seqlens_host[pb->num_seqs];
   auto whole_tiles = [](int64_t keys) { return (keys + 63) / 64 * 64; };
   p.few_chunk = (int)std::max(
       std::min<int64_t>(1024, std::max<int64_t>(128, whole_tiles(lh * ntot / 256))),
-      whole_tiles((max_seqlen(pb) + 511) / 512));
+      whole_tiles(((int64_t)max_seqlen(pb) + 511) / 512));
   p.few_total_chunks = (int)chunks_for(p.few_chunk);
   p.few_slots = (ntot + 15) / 16 * 16 + 16 * (int64_t)pb->num_seqs;
+  p.few_heads = 0;
+  if (p.few) {
+    // in every room alike: one head's logits fit the static scratch
+    const size_t base = layout(pb, p).sal, head = few_head_bytes(p);  // base: without logits
+    p.few = base + align_up(head) <= kStaticScratchBytes;
+    if (p.few) {
+      const int64_t most_heads = (int64_t)((room - base) / head);
+      const int64_t groups = (lh + most_heads - 1) / most_heads;
+      p.few_heads = (int)((lh + groups - 1) / groups);
+    }
+  }
   return p;
-}
-
-struct WsLayout {
-  size_t partial, lse, cnt, logits, sal, total;
-};
-
-WsLayout layout(const stepkv_problem* pb, const SaliencyPlan& p) {
-  const size_t lh = (size_t)pb->num_layers * pb->num_kv_heads;
-  const size_t ntot = (size_t)pb->cu_seqlens_host[pb->num_seqs];
-  WsLayout w;
-  size_t off = 0;
-  w.partial = off;  // sized for the longest chunk list of the plans
-  off = align_up(off + sizeof(float) * 2 * lh *
-                           std::max((size_t)std::max(p.total_chunks, p.fused_total_chunks) * p.rows_pad,
-                                    p.few ? (size_t)p.few_total_chunks * 16 : 0));
-  w.lse = off;
-  off = align_up(off + sizeof(float) * pb->num_seqs * lh * p.rows_pad);
-  w.cnt = off;  // per (sequence, head) counters of the one-launch sweeps
-  off = align_up(off + sizeof(int32_t) * pb->num_seqs * lh);
-  w.logits = off;
-  if (p.few) off = align_up(off + sizeof(float) * lh * p.few_slots * 4 * few_rows_quads(p.R));
-  w.sal = off;
-  off = align_up(off + sizeof(float) * lh * ntot);
-  w.total = off;
-  return w;
 }
 
 int hip_status(hipError_t e) { return e == hipSuccess ? STEPKV_OK : STEPKV_EHIP; }
@@ -299,12 +323,13 @@ int stepkv_step_update(stepkv_step_state* st, float valid, float gain, float red
 
 size_t stepkv_score_workspace_bytes(const stepkv_problem* pb) {
   if (check_problem(pb) != STEPKV_OK) return 0;
-  return layout(pb, plan_saliency(pb)).total;
+  return layout(pb, plan_saliency(pb, kWideRoomBytes)).total;
 }
 
 size_t stepkv_saliency_workspace_bytes(const stepkv_problem* pb) {
   if (check_problem(pb) != STEPKV_OK) return 0;
-  return layout(pb, plan_saliency(pb)).sal;  // everything but the saliency buffer
+  // everything but the saliency buffer
+  return layout(pb, plan_saliency(pb, kStaticScratchBytes)).sal;
 }
 
 }  // extern "C"
@@ -382,7 +407,13 @@ int run_saliency(const stepkv_problem* pb, const stepkv_params* prm, const Salie
     sa.R = plan.R;
     sa.rows_pad = plan.rows_pad;
     sa.accumulate = 0;
-    return hip_status(launch_few_rows(sa, d, st));
+    const int lh = sa.L * sa.Hkv;
+    for (int lh0 = 0; lh0 < lh; lh0 += plan.few_heads) {
+      const int rc =
+          hip_status(launch_few_rows(sa, d, lh0, std::min(plan.few_heads, lh - lh0), st));
+      if (rc != STEPKV_OK) return rc;
+    }
+    return STEPKV_OK;
   }
   // Window rows in groups of at most 256, one pair of sweeps per group: a
   // row's LSE needs only its own logits, and the column sums of the later
@@ -525,6 +556,18 @@ CompressLayout compress_layout(const stepkv_problem* pb, const SaliencyPlan& pla
   return c;
 }
 
+// The plan of a call with ws_bytes of workspace, of which a plan takes need(plan):
+// smaller groups of few rows where the wide room's do not fit, and two sweeps
+// where the call keeps no logits (row LSEs in or out, a forced schedule) or has
+// no room for either.
+template <typename Need>
+SaliencyPlan plan_call(const stepkv_problem* pb, bool keeps_logits, size_t ws_bytes, Need need) {
+  SaliencyPlan p = plan_saliency(pb, kWideRoomBytes);
+  if (p.few && keeps_logits && ws_bytes < need(p)) p = plan_saliency(pb, kStaticScratchBytes);
+  if (p.few && (!keeps_logits || ws_bytes < need(p))) p.few = false;
+  return p;
+}
+
 }  // namespace
 
 extern "C" {
@@ -536,7 +579,8 @@ int stepkv_saliency(const stepkv_problem* pb, const stepkv_params* prm, const vo
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !saliency) return STEPKV_EINVAL;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan = plan_call(
+      pb, prm->saliency_schedule == 0, ws_bytes, [&](const SaliencyPlan& p) { return layout(pb, p).sal; });
   const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
@@ -571,7 +615,8 @@ int stepkv_score(const stepkv_problem* pb, const stepkv_params* prm, const void*
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan = plan_call(
+      pb, prm->saliency_schedule == 0, ws_bytes, [&](const SaliencyPlan& p) { return layout(pb, p).total; });
   const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
@@ -596,10 +641,8 @@ int stepkv_score_noalloc(const stepkv_problem* pb, const stepkv_params* prm, con
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  // the sweeps' workspace (everything but the saliency buffer, which the caller
-  // passes), with the logits of few window rows where they fit
-  SaliencyPlan plan = plan_saliency(pb);
-  if (plan.few && layout(pb, plan).sal > kStaticScratchBytes) plan = plan_saliency(pb, false);
+  // the sweeps' workspace (everything but the saliency buffer, which the caller passes)
+  const SaliencyPlan plan = plan_saliency(pb, kStaticScratchBytes);
   if (layout(pb, plan).sal > kStaticScratchBytes) return STEPKV_ESCRATCH;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
   void* ws = nullptr;
@@ -618,7 +661,8 @@ int stepkv_window_lse(const stepkv_problem* pb, const stepkv_params* prm, const 
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !lse_win) return STEPKV_EINVAL;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan = plan_call(
+      pb, false, ws_bytes, [&](const SaliencyPlan& p) { return layout(pb, p).sal; });
   const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   // runs even without keys: every row then sees none and gets -inf
@@ -633,7 +677,8 @@ int stepkv_saliency_from_lse(const stepkv_problem* pb, const stepkv_params* prm,
   if (rc == STEPKV_OK) rc = check_params(pb, prm);
   if (rc != STEPKV_OK) return rc;
   if (!q_win || !k || !lse_win || !saliency) return STEPKV_EINVAL;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan = plan_call(
+      pb, false, ws_bytes, [&](const SaliencyPlan& p) { return layout(pb, p).sal; });
   const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.sal || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
@@ -653,7 +698,8 @@ int stepkv_score_from_lse(const stepkv_problem* pb, const stepkv_params* prm, co
   rc = check_priority_args(pb, step_ids, protected_mask, step_utility, scores, step_stats,
                            saliency, (size_t)pb->num_layers * pb->num_kv_heads);
   if (rc != STEPKV_OK) return rc;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan = plan_call(
+      pb, false, ws_bytes, [&](const SaliencyPlan& p) { return layout(pb, p).total; });
   const WsLayout w = layout(pb, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   if (pb->cu_seqlens_host[pb->num_seqs] == 0) return STEPKV_OK;
@@ -670,7 +716,7 @@ size_t stepkv_score_shared_workspace_bytes(const stepkv_problem* pb, int32_t las
   if (check_problem(pb) != STEPKV_OK || last_layers < 1) return 0;
   const int n = shared_layers(pb, last_layers);
   const stepkv_problem sub = last_layers_view(pb, n);
-  return shared_layout(pb, n, sub, plan_saliency(&sub)).total;
+  return shared_layout(pb, n, sub, plan_saliency(&sub, kWideRoomBytes)).total;
 }
 
 int stepkv_score_shared(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
@@ -688,7 +734,9 @@ int stepkv_score_shared(const stepkv_problem* pb, const stepkv_params* prm, cons
   if (rc != STEPKV_OK) return rc;
   const int n = shared_layers(pb, last_layers);
   const stepkv_problem sub = last_layers_view(pb, n);
-  const SaliencyPlan plan = plan_saliency(&sub);
+  const SaliencyPlan plan =
+      plan_call(&sub, !lse_win && prm->saliency_schedule == 0, ws_bytes,
+                [&](const SaliencyPlan& p) { return shared_layout(pb, n, sub, p).total; });
   const SharedLayout w = shared_layout(pb, n, sub, plan);
   if (!workspace || ws_bytes < w.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   const int ntot = pb->cu_seqlens_host[pb->num_seqs];
@@ -812,7 +860,7 @@ int stepkv_compact(const stepkv_problem* pb, const void* k, const void* v, const
 
 size_t stepkv_compress_workspace_bytes(const stepkv_problem* pb) {
   if (check_problem(pb) != STEPKV_OK) return 0;
-  return compress_layout(pb, plan_saliency(pb)).total;
+  return compress_layout(pb, plan_saliency(pb, kWideRoomBytes)).total;
 }
 
 int stepkv_compress(const stepkv_problem* pb, const stepkv_params* prm, const void* q_win,
@@ -830,7 +878,9 @@ int stepkv_compress(const stepkv_problem* pb, const stepkv_params* prm, const vo
   if (out_rows > 0 && (!k_out || !v_out)) return STEPKV_EINVAL;  // NULL outputs hold 0 rows
   if (!step_utility && pb->cu_steps_host[pb->num_seqs] > 0) return STEPKV_EINVAL;
   if (!budgets && budget < 1) return STEPKV_EINVAL;
-  const SaliencyPlan plan = plan_saliency(pb);
+  const SaliencyPlan plan =
+      plan_call(pb, !lse_win && prm->saliency_schedule == 0, ws_bytes,
+                [&](const SaliencyPlan& p) { return compress_layout(pb, p).total; });
   const CompressLayout cl = compress_layout(pb, plan);
   if (!workspace || ws_bytes < cl.total || !aligned(workspace)) return STEPKV_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);

@@ -10,7 +10,7 @@
 // (8 KV heads, d 128), both sweeps in one launch and this form: one query per
 // head (R = 4) 601 -> 409 us (K at 5.7 TB/s and 27 us for the sums), R = 8
 // 602 -> 460; d 64: 316 -> 238 and 316 -> 277; one layer of 8192 tokens
-// 17.6 -> 13.1 (a launch less).
+// 17.6 -> 12.4 (a launch less).
 #include "common.h"
 #include "internal.h"
 #include "saliency_chunks.h"
@@ -82,20 +82,21 @@ __device__ __forceinline__ size_t logit_slot(int s, int seq0) {
 // l % 16 for rows 4 (l / 16) + 0..3. Rings of 2 and 4 tiles: 413 and 404 us here,
 // 52 and 57 against 52 on three layers (fewer workgroups fit a CU).
 template <int D, int RQ, bool CAUSAL>
-__global__ __launch_bounds__(kThreads) void row_logits_kernel(SaliencyArgs a) {
+__global__ __launch_bounds__(kThreads) void row_logits_kernel(SaliencyArgs a, int lh0) {
   constexpr int KS = D / 32;
   __shared__ __attribute__((aligned(16))) uint8_t kring[(kThreads / kWave) * kRing * 32 * D];
   __shared__ float2 part[kThreads / kWave][kMaxFewRows];
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int c16 = lane & 15, g4 = lane >> 4;
-  const int lh = blockIdx.x / a.total_chunks, g = blockIdx.x - lh * a.total_chunks;
+  const int lr = blockIdx.x / a.total_chunks, g = blockIdx.x - lr * a.total_chunks;
+  const int lh = lh0 + lr;
   const ChunkLoc loc = find_chunk(a, g);
   const int l = lh / a.Hkv, h = lh - l * a.Hkv;
   const int key0 = (g - loc.first) * a.chunk;
   const int nkeys = min(a.chunk, loc.ns - key0);
   const int ntiles = (nkeys + 15) / 16;
   const uint16_t* __restrict__ kb = a.k + ((size_t)lh * a.ntot + loc.seq0 + key0) * D;
-  float* __restrict__ lg = a.logits + ((size_t)lh * a.logit_slots + logit_slot(loc.s, loc.seq0) +
+  float* __restrict__ lg = a.logits + ((size_t)lr * a.logit_slots + logit_slot(loc.s, loc.seq0) +
                                        key0) * (4 * RQ) + 64 * g4 + 4 * c16;
   // K ring of this wave in LDS: kRing tiles of 16 rows, each row's 16-byte pieces
   // XOR-swizzled
@@ -203,15 +204,14 @@ __global__ __launch_bounds__(kThreads) void row_logits_kernel(SaliencyArgs a) {
   }
 }
 
-// One workgroup per (head, chunk), the heads in reverse (the logits written
-// last are still in the caches).
+// One workgroup per (head, chunk) of the launch, the heads in reverse (the
+// logits written last are still in the caches).
 template <int RQ>
-__global__ __launch_bounds__(kThreads) void row_sums_kernel(SaliencyArgs a) {
+__global__ __launch_bounds__(kThreads) void row_sums_kernel(SaliencyArgs a, int lh0, int heads) {
   __shared__ float2 part[kThreads / kWave][kMaxFewRows];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int LH = a.L * a.Hkv;
-  const int lr = blockIdx.x / a.total_chunks, g = blockIdx.x - lr * a.total_chunks;
-  const int lh = LH - 1 - lr;
+  const int b = blockIdx.x / a.total_chunks, g = blockIdx.x - b * a.total_chunks;
+  const int lr = heads - 1 - b, lh = lh0 + lr;
   const ChunkLoc loc = find_chunk(a, g);
   const int nch = chunks_of(a, loc.s);
   const int key0 = (g - loc.first) * a.chunk;
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void row_sums_kernel(SaliencyArgs a) {
 #pragma unroll
   for (int r = 0; r < 4 * RQ; ++r) lse[r] = __shfl(l2, r, kWave);
   const float* __restrict__ lg =
-      a.logits + ((size_t)lh * a.logit_slots + logit_slot(loc.s, loc.seq0) + key0) * (4 * RQ);
+      a.logits + ((size_t)lr * a.logit_slots + logit_slot(loc.s, loc.seq0) + key0) * (4 * RQ);
   float* __restrict__ out = a.sal + (size_t)lh * a.ntot + loc.seq0 + key0;
   for (int e = tid; e < nkeys; e += kThreads) {
     const float* __restrict__ p = lg + (size_t)(e >> 4) * (64 * RQ) + 4 * (e & 15);
@@ -266,19 +266,20 @@ __global__ __launch_bounds__(kThreads) void row_sums_kernel(SaliencyArgs a) {
 }
 
 template <int D, int RQ>
-hipError_t launch_few_rows_q(const SaliencyArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.L * a.Hkv) * (unsigned)a.total_chunks);
+hipError_t launch_few_rows_q(const SaliencyArgs& a, int lh0, int heads, hipStream_t st) {
+  const dim3 grid((unsigned)heads * (unsigned)a.total_chunks);
   if (a.causal)
-    hipLaunchKernelGGL((row_logits_kernel<D, RQ, true>), grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((row_logits_kernel<D, RQ, true>), grid, dim3(kThreads), 0, st, a, lh0);
   else
-    hipLaunchKernelGGL((row_logits_kernel<D, RQ, false>), grid, dim3(kThreads), 0, st, a);
-  hipLaunchKernelGGL(row_sums_kernel<RQ>, grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((row_logits_kernel<D, RQ, false>), grid, dim3(kThreads), 0, st, a, lh0);
+  hipLaunchKernelGGL(row_sums_kernel<RQ>, grid, dim3(kThreads), 0, st, a, lh0, heads);
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_few_rows_d(const SaliencyArgs& a, hipStream_t st) {
-  return a.R <= 4 ? launch_few_rows_q<D, 1>(a, st) : launch_few_rows_q<D, 2>(a, st);
+hipError_t launch_few_rows_d(const SaliencyArgs& a, int lh0, int heads, hipStream_t st) {
+  return a.R <= 4 ? launch_few_rows_q<D, 1>(a, lh0, heads, st)
+                  : launch_few_rows_q<D, 2>(a, lh0, heads, st);
 }
 
 }  // namespace
@@ -289,8 +290,9 @@ hipError_t launch_few_rows_d(const SaliencyArgs& a, hipStream_t st) {
 bool few_rows(int R) { return R <= kFewRows; }
 int few_rows_quads(int R) { return R <= 4 ? 1 : 2; }
 
-hipError_t launch_few_rows(const SaliencyArgs& a, int d, hipStream_t st) {
-  return d == 128 ? launch_few_rows_d<128>(a, st) : launch_few_rows_d<64>(a, st);
+hipError_t launch_few_rows(const SaliencyArgs& a, int d, int lh0, int heads, hipStream_t st) {
+  return d == 128 ? launch_few_rows_d<128>(a, lh0, heads, st)
+                  : launch_few_rows_d<64>(a, lh0, heads, st);
 }
 
 }  // namespace stepkv

@@ -33,8 +33,8 @@ struct SaliencyArgs {
   int* unit_cnt;
   int lag;
   uint32_t* status;  // device status word (STEPKV_FLAG_*) or null
-  // few window rows: the logits [L*Hkv][logit_slots][4 * few_rows_quads(R)],
-  // and partial is [L*Hkv][total_chunks][16]
+  // few window rows: the logits [heads of a launch][logit_slots][4 *
+  // few_rows_quads(R)], and partial is [L*Hkv][total_chunks][16]
   float* logits;
   int64_t logit_slots;
   // Batches of at most kArgSeqs sequences also pass cu_seqlens and each
@@ -57,11 +57,11 @@ enum class SaliencyMode { kBoth, kLseOnly, kFromLse };
 hipError_t launch_saliency(const SaliencyArgs& a, int d, SaliencyMode mode, hipStream_t st);
 
 // Few window rows (all of them in one group): K read once and the logits kept
-// (both sweeps' work; no row LSE is exported). few_rows: whether R rows take
-// this form.
+// (both sweeps' work; no row LSE is exported), for the (layer, KV head) pairs
+// lh0 .. lh0 + heads - 1. few_rows: whether R rows take this form.
 bool few_rows(int R);
 int few_rows_quads(int R);
-hipError_t launch_few_rows(const SaliencyArgs& a, int d, hipStream_t st);
+hipError_t launch_few_rows(const SaliencyArgs& a, int d, int lh0, int heads, hipStream_t st);
 
 // ---------------------------------------------------------------- fuse
 struct FuseArgs {

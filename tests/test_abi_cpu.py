@@ -125,6 +125,25 @@ def test_workspace_bytes(lib):
     assert lib.stepkv_score_workspace_bytes(ctypes.byref(_problem(Hq=7))) == 0
 
 
+@pytest.mark.parametrize("W,G", [(1, 1), (1, 4), (2, 4), (1, 7)])
+def test_few_rows_workspace_is_bounded(lib, W, G):
+    """The logits of at most 8 window rows take a bounded room, whatever the cache: the static
+    scratch holds stepkv_saliency's workspace, and a pass takes 272 MiB beside its saliency."""
+    for L, H, n in ((1, 2, 1024), (32, 8, 32768), (32, 8, 131072)):
+        pb = _problem(L=L, Hq=H * G, Hkv=H, W=W, cu=(0, n), cu_steps=(0, 4))
+        P = ctypes.byref(pb)
+        heads = -(-4 * L * H * n // 256) * 256
+        assert 0 < lib.stepkv_saliency_workspace_bytes(P) <= B.STATIC_SCRATCH_BYTES
+        score = lib.stepkv_score_workspace_bytes(P)
+        assert score <= heads + (272 << 20)
+        assert lib.stepkv_compress_workspace_bytes(P) <= 3 * heads + (272 << 20)
+        assert lib.stepkv_score_shared_workspace_bytes(P, L) <= heads + (272 << 20) + 8 * n + 4096
+        assert lib.stepkv_saliency_workspace_bytes(P) + heads <= score
+    # one head's logits past the static scratch: none are kept
+    big = _problem(L=1, Hq=G, Hkv=1, W=W, cu=(0, 9_000_000), cu_steps=(0, 4))
+    assert lib.stepkv_saliency_workspace_bytes(ctypes.byref(big)) < 16 * 9_000_000
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(Hq=7), B.EINVAL),          # G not an integer
     (dict(d=96), B.EUNSUPPORTED),    # head dim

@@ -165,3 +165,88 @@ def test_long_sequence_is_not_slower_than_two_sweeps():
     t = {s: sorted(passes(s) for _ in range(5))[2] for s in (0, 1)}
     torch.testing.assert_close(out[0], out[1], rtol=1.1e-5, atol=1e-12)
     assert t[0] < 1.3 * t[1], t
+
+
+def _random_cache(L, H, G, W, d, n, seed=7):
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q, k = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            for s in ((L, 1, W, H * G, d), (L, H, n, d)))
+    steps = 20
+    pb = B.Problem(L, H * G, H, d, W, np.array([0, n]), np.array([0, steps]))
+    sid = (torch.arange(n, device="cuda") * steps // n).to(torch.int32)
+    prot = (torch.arange(n, device="cuda") < 40).to(torch.uint8)
+    util = torch.rand(steps, generator=gen, device="cuda")
+    return pb, q, k, sid, prot, util
+
+
+def test_workspace_of_a_wider_window_serves_few_rows():
+    """A workspace sized for the same cache at window 64 has no room for logits: every entry point
+    takes it and reads K twice, as the two-sweep schedule does."""
+    import ctypes
+
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    L, H, G, d, n, budget = 4, 4, 4, 128, 9000, 300
+    lib = B.load()
+    wide = B.Problem(L, H * G, H, d, 64, np.array([0, n]), np.array([0, 20]))
+    size = {"saliency": wide.saliency_workspace_bytes(), "score": wide.workspace_bytes(),
+            "compress": int(lib.stepkv_compress_workspace_bytes(ctypes.byref(wide.c))),
+            "shared": int(lib.stepkv_score_shared_workspace_bytes(ctypes.byref(wide.c), 3))}
+    pb, q, k, sid, prot, util = _random_cache(L, H, G, 1, d, n)
+    assert size["saliency"] < pb.saliency_workspace_bytes()  # less than what holds the logits
+    ws = {key: torch.empty(b, dtype=torch.uint8, device="cuda") for key, b in size.items()}
+    rows = int(pb.retained_rows(prot.cpu().numpy(), budget)[-1])
+    lse = B.window_lse(pb, q, k, workspace=ws["saliency"])
+    res = {}
+    for sched in (0, 1):
+        prm = B.Params(saliency_schedule=sched)
+        log(f"[few rows, workspace of window 64] schedule {sched}")
+        out = [B.saliency(pb, q, k, prm, workspace=ws["saliency"]),
+               B.saliency_from_lse(pb, q, k, lse, prm, workspace=ws["saliency"])]
+        for kw in ({}, {"lse": lse}):
+            out.append(B.score(pb, q, k, sid, prot, util, prm, workspace=ws["score"], **kw)["scores"])
+            c = B.compress(pb, q, k, k, sid, prot, util, budget, rows, prm,
+                           workspace=ws["compress"], **kw)
+            out += [c["scores"], c["k_hat"]]
+            out.append(B.score_shared(pb, q, k, sid, prot, util, prm, workspace=ws["shared"],
+                                      **kw)["scores"])
+        res[sched] = out
+    for a, b in zip(res[0], res[1]):
+        assert torch.equal(a, b)
+    with pytest.raises(B.StepKVError):  # and still none below the sweeps' own need
+        B.saliency(pb, q, k, workspace=ws["saliency"][:1024])
+    ample = B.saliency(pb, q, k)  # the logits kept
+    torch.testing.assert_close(ample, res[0][0], rtol=1.1e-5, atol=1e-12)
+
+
+@pytest.mark.parametrize("G,n,groups", [(4, 32768, 2), (8, 32768, 3), (2, 6000, 1)])
+def test_few_rows_in_groups_of_heads(G, n, groups):
+    """32 layers x 8 heads: the logits in one group (a whole pass' workspace), in the groups that
+    stepkv_saliency's own size makes and in those of the static scratch agree bit for bit."""
+    import ctypes
+
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    pb, q, k, sid, prot, util = _random_cache(32, 8, G, 1, 64, n)
+    need, logits = pb.saliency_workspace_bytes(), 32 * 8 * n * 16 * (1 if G <= 4 else 2)
+    assert need <= B.STATIC_SCRATCH_BYTES
+    assert logits // groups <= need < logits // groups + (8 << 20)
+    log(f"[few rows G={G} n={n}]")
+    full = B.score(pb, q, k, sid, prot, util, want_saliency=True)
+    A = B.saliency(pb, q, k)  # its own workspace size
+    assert torch.equal(A, full["saliency"])
+    scores, sal = torch.empty_like(A), torch.empty_like(A)
+    rc = B.load().stepkv_score_noalloc(
+        ctypes.byref(pb.c), ctypes.byref(B.Params().c()), q.data_ptr(), k.data_ptr(),
+        sid.data_ptr(), prot.data_ptr(), util.data_ptr(), scores.data_ptr(), sal.data_ptr(), None,
+        B._stream(None))
+    assert rc == 0
+    assert torch.equal(sal, A) and torch.equal(scores, full["scores"])
