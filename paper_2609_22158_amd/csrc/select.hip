@@ -706,8 +706,9 @@ constexpr int kRankHalf = 4;
 constexpr int kRankBlocks = 8;
 
 // What rank_row holds in place of U for a protected token or a position past
-// the sequence: a NaN that no sum of saliencies produces, passed over by fmaxf.
-constexpr uint32_t kNoU = 0xFFFFFFFFu;
+// the sequence: below every U, which is a sum of exponentials (0 or more, or NaN
+// of any payload), so u < 0 means masked and the maximum from 0 passes it over.
+constexpr float kNoU = -1.f;
 
 // The masked saliency at the ends of every wave's 256 positions, where the
 // neighbouring wave's pooling reads it: run q of 256 positions is entry q + 1,
@@ -798,7 +799,7 @@ __device__ __forceinline__ void rank_row(const FuseArgs& f, const SelectArgs& a,
       float acc = v[4 + e - HALF];
 #pragma unroll
       for (int o = 1; o <= 2 * HALF; ++o) acc += v[4 + e - HALF + o];
-      u[b][e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? acc : __uint_as_float(kNoU);
+      u[b][e] = ((pw[b] >> (8 * e)) & 0xFFu) == 0u ? acc : kNoU;
       m = fmaxf(m, u[b][e]);
     }
   }
@@ -835,7 +836,7 @@ __device__ __forceinline__ void rank_row(const FuseArgs& f, const SelectArgs& a,
     float pv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool pr = __float_as_uint(u[b][e]) != kNoU;
+      const bool pr = !(u[b][e] < 0.f);
       const float bu = bu_lds[min((uint32_t)kk[b][e], (uint32_t)nsteps)];
       const float p = fmaf(f.alpha, u[b][e] * inv, bu);
       if (FLAGS) {

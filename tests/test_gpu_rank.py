@@ -52,3 +52,37 @@ def test_compress_equals_score_and_select(lengths, pool):
         a = int(w.cu_seqlens[s])
         n = int(c[s + 1] - c[s])
         assert np.array_equal(got[:, :, a:a + n], want[:, :, a:a + n])
+
+
+@pytest.mark.parametrize("bits", [0x7FC00000, 0xFFFFFFFF, 0xFFC00001])
+def test_compress_from_nan_lse(bits):
+    """A NaN row LSE of any payload leaves NaN priorities (ranked as -inf, flagged), never a
+    token that counts as protected."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    w = make_workload("l1_8k", seqlens=[3000, 5000], num_layers=1, protected_len=0, budget=300)
+    pb = B.Problem.from_workload(w)
+    q, k, v = (B.bf16_from_bits(x) for x in (w.q_win, w.k, w.v))
+    rng = np.random.default_rng(1)
+    prot = (rng.random(w.total_tokens) < 0.03).astype(np.uint8)
+    sid, pdev = torch.from_numpy(w.step_ids).cuda(), torch.from_numpy(prot).cuda()
+    util = torch.from_numpy(gpu_utilities(w)).cuda()
+    lse = B.window_lse(pb, q, k)
+    lse.view(torch.int32)[0, 0, 5, 0] = bits - (1 << 32) if bits >> 31 else bits  # head 0
+    pb.status(clear=True)
+    log(f"[rank NaN lse {bits:#x}]")
+    P = B.score(pb, q, k, sid, pdev, util, lse=lse)["scores"]
+    idx, cu, _ = B.select(pb, P, pdev, sid, w.budget)
+    flags = pb.status(clear=True)
+    res = B.compress(pb, q, k, v, sid, pdev, util, w.budget, w.total_tokens, lse=lse)
+    assert flags & B.FLAG_NONFINITE and pb.status(clear=True) == flags
+    assert torch.equal(res["cu_retained"], cu)
+    # NaN payloads may differ between the kernels, so NaN as NaN, everything else bit for bit
+    nan = torch.isnan(P)
+    assert bool(nan.any()) and torch.equal(torch.isnan(res["scores"]), nan)
+    assert torch.equal(res["scores"].masked_fill(nan, 0.0), P.masked_fill(nan, 0.0))
+    for s in range(w.num_seqs):
+        a, n = int(w.cu_seqlens[s]), int(cu[s + 1] - cu[s])
+        assert torch.equal(res["idx"][:, :, a:a + n], idx[:, :, a:a + n])
