@@ -417,8 +417,12 @@ def _stream(stream) -> int:
         return int(stream.cuda_stream)
     import torch
 
-    # the raw handle, without a Stream object around it (1.5 us of a short call)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the raw handle, without a Stream object around it (1.5 us of a short call),
+    # where this torch has the call for it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return raw(torch.cuda.current_device())
 
 
 def _need(t, dtype, shape, name):

@@ -46,6 +46,18 @@ def test_defaults_are_the_papers(lib):
     assert p.causal_tail == 0  # every window row sees the whole sequence unless asked
 
 
+def test_current_stream_without_the_private_call(monkeypatch):
+    """The current stream's handle comes from torch's public call where the raw one is absent."""
+    import types
+
+    import torch
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert B._stream(None) == 77
+    assert B._stream(types.SimpleNamespace(cuda_stream=78)) == 78
+
+
 def test_strerror(lib):
     assert B.strerror(0) == "ok"
     assert "workspace" in B.strerror(-3)
