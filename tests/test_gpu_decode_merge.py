@@ -1,6 +1,7 @@
 """Decode: splits shared by 4, 8 and 16 waves and the three forms of the merge (all heads of a
-KV head per workgroup; one head with one or several thread groups over the splits), with more
-than 64 splits per sequence, empty and one-row sequences and an out_rows that cuts the last one.
+KV head per workgroup; one head with one or several thread groups over the splits), each with
+one split, a few and more than 64 per sequence, empty and one-row sequences and an out_rows that
+cuts the last one.
 P enters the second product as two bf16 parts (2^-17 relative) and every sum is fp32, so an
 output differs from float64 attention by less than 2^-15 of its row's largest magnitude."""
 import numpy as np
@@ -19,6 +20,12 @@ CASES = {
     "one_head_128": (16, 64, 8, 128, [300, 77], 0),
     "all_heads": (16, 28, 4, 64, [100, 600, 0, 1300, 64, 1, 900, 513], 300),
     "all_heads_split1024": (32, 16, 8, 64, [7000, 1, 300], 0),
+    # kv heads x sequences >= 512: all heads per workgroup, 79 splits in one sequence
+    "all_heads_many_splits": (1, 7, 1, 64, [3, 40000, 2600] + [0, 1, 17] * 180, 0),
+    "all_heads_many_splits_d128": (2, 6, 2, 128, [33300, 700] + [0, 5] * 90, 3),
+    # fewer, but 1024 query heads: 128 threads per head; 1, 6 and 79 splits
+    "one_head_128_splits": (1, 8, 1, 64, [3000, 40000, 1] + [0, 20] * 70, 0),
+    "one_head_128_splits_d128": (2, 64, 4, 128, [2700, 33300] + [0, 9] * 10, 5),
 }
 
 

@@ -1,7 +1,8 @@
 """The one-launch priority and selection of stepkv_compress against stepkv_score and
 stepkv_select, bit for bit: row lengths around the waves' 256 positions and the blocks of 4096,
 pooling windows 1 to 9 (in registers) and 11 (the separate kernels), protected tokens and
-out-of-range step ids anywhere, a NaN key, and the status word's flags."""
+out-of-range step ids anywhere, a NaN key, and the status word's flags; the same without a
+status word; and step counts around the table that it keeps in LDS."""
 import numpy as np
 import pytest
 
@@ -47,11 +48,45 @@ def test_compress_equals_score_and_select(lengths, pool):
     assert bool(flags & B.FLAG_NONFINITE) == (pool == 3)
     assert np.array_equal(res["scores"].cpu().numpy().view(np.uint32), P.cpu().numpy().view(np.uint32))
     assert np.array_equal(res["cu_retained"].cpu().numpy(), cu.cpu().numpy())
+    quiet = B.Problem.from_workload(w, status=False)  # code of its own, without the flags
+    log(f"[rank {lengths} pool={pool}] compress without a status word")
+    other = B.compress(quiet, q, k, v, sid, pdev, util, w.budget, rows, prm)
+    for key in ("scores", "cu_retained"):
+        assert torch.equal(other[key].view(torch.int32), res[key].view(torch.int32)), key
     c, got, want = cu.cpu().numpy(), res["idx"].cpu().numpy(), idx.cpu().numpy()
+    bare = other["idx"].cpu().numpy()
     for s in range(w.num_seqs):
         a = int(w.cu_seqlens[s])
         n = int(c[s + 1] - c[s])
         assert np.array_equal(got[:, :, a:a + n], want[:, :, a:a + n])
+        assert np.array_equal(bare[:, :, a:a + n], want[:, :, a:a + n])
+
+
+@pytest.mark.parametrize("steps", [0, 1, 4096, 4097])
+def test_compress_step_counts(steps):
+    """Steps in a sequence up to 4096 (the ranking's table of utilities) and one more (the
+    separate kernels), and none at all."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    n, L, H = 9001, 2, 2
+    gen = torch.Generator(device="cuda").manual_seed(steps)
+    q, k = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            for s in ((L, 1, 16, 4 * H, 128), (L, H, n, 128)))
+    pb = B.Problem(L, 4 * H, H, 128, 16, np.array([0, n]), np.array([0, steps]))
+    # every step id occurs, the last one among them
+    sid = (torch.arange(n, device="cuda") * max(steps, 1) // n).to(torch.int32)
+    prot = (torch.arange(n, device="cuda") % 37 == 0).to(torch.uint8)
+    util = torch.rand(steps, generator=gen, device="cuda")
+    rows = int(pb.retained_rows(prot.cpu().numpy(), 500)[-1])
+    log(f"[rank {steps} steps]")
+    P = B.score(pb, q, k, sid, prot, util)["scores"]
+    idx, cu, _ = B.select(pb, P, prot, sid, 500)
+    res = B.compress(pb, q, k, k, sid, prot, util, 500, rows)
+    assert bool(pb.status() & B.FLAG_STEP_ID) == (steps == 0)
+    assert torch.equal(res["scores"], P) and torch.equal(res["cu_retained"], cu)
+    assert torch.equal(res["idx"][:, :, :rows], idx[:, :, :rows])
 
 
 @pytest.mark.parametrize("bits", [0x7FC00000, 0xFFFFFFFF, 0xFFC00001])
