@@ -179,13 +179,21 @@ def record_traffic(args) -> None:
     print(json.dumps(db[key]))
 
 
+# what the sweeps' traffic depends on: their kernels, the chunk lookup and the headers they
+# include, and the host code that plans chunks and schedules
+TRAFFIC_SOURCES = ("saliency.hip", "saliency_chunks.h", "common.h", "internal.h", "api.cpp")
+
+
 def source_digest() -> str:
-    """sha256 of the saliency kernel source: traffic figures are valid for it only."""
+    """sha256 of the sources behind the saliency sweeps: traffic figures are valid for them only."""
     import hashlib
 
-    path = os.path.join(ROOT, "paper_2609_22158_amd", "csrc", "saliency.hip")
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    digest = hashlib.sha256()
+    for name in TRAFFIC_SOURCES:
+        with open(os.path.join(ROOT, "paper_2609_22158_amd", "csrc", name), "rb") as f:
+            digest.update(f.read())
+        digest.update(b"\0")
+    return digest.hexdigest()
 
 
 def traffic_key(workload: str, budget: int, window: int, lse_fed: bool, shared_layers: int = 0,

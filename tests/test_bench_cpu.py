@@ -1,6 +1,7 @@
 """Host logic of bench.py: which committed traffic record a bench line may use."""
 import json
 import os
+import shutil
 
 import bench
 
@@ -27,3 +28,18 @@ def test_recorded_traffic_only_for_recorded_shapes():
     for key in recorded:
         rec = json.load(open(path))[key]
         assert rec["hbm_bytes_per_launch"] == rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"]
+
+
+def test_traffic_records_follow_every_source_of_the_sweeps(tmp_path, monkeypatch):
+    """An edit to the sweeps, their chunk lookup or the planning makes the records stale."""
+    src = os.path.join(bench.ROOT, "paper_2609_22158_amd", "csrc")
+    dst = tmp_path / "paper_2609_22158_amd" / "csrc"
+    shutil.copytree(src, dst)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    start = bench.source_digest()
+    for name in ("saliency.hip", "saliency_chunks.h", "api.cpp", "internal.h", "common.h"):
+        text = (dst / name).read_bytes()
+        (dst / name).write_bytes(text + b"\n// edited")
+        assert bench.source_digest() != start, name
+        (dst / name).write_bytes(text)
+    assert bench.source_digest() == start
