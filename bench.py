@@ -155,6 +155,8 @@ def record_traffic(args) -> None:
         out[counter] = {"calibration": cal, "launches": launches,
                         "bytes": sum(sum(v) for v in per_kernel.values()) / launches,
                         "per_kernel": {k: sum(v) / launches for k, v in per_kernel.items()}}
+    if not launches:
+        sys.exit("no column-sum sweep in these counters (few window rows read K once)")
     budget = args.budget or 1024
     key = traffic_key(args.workload, budget, args.window or 64, args.lse_fed, args.shared_layers,
                       args.schedule)
@@ -204,6 +206,15 @@ def traffic_key(workload: str, budget: int, window: int, lse_fed: bool, shared_l
     return (f"{workload}_b{budget}_w{window}" + ("_lse" if lse_fed else "")
             + (f"_shared{shared_layers}" if shared_layers > 0 else "")
             + (f"_schedule{schedule}" if schedule else ""))
+
+
+def saliency_form(rows: int, lse_fed: bool, schedule: int):
+    """Passes over K of the saliency stage for `rows` window rows (W * G), and their name."""
+    if lse_fed:
+        return 1, "saliency (one MFMA sweep over K, row LSE given)"
+    if rows <= 8 and schedule == 0:
+        return 1, "saliency (K read once, the logits of few window rows kept)"
+    return 2, "saliency (two MFMA sweeps over K)"
 
 
 def recorded_traffic(key: str):
@@ -581,7 +592,7 @@ def main():
     lh = L * Hkv
     # algorithmic work per launch of the saliency stage (in shared mode: the
     # scoring call, whose sweeps cover the last n layers only)
-    sweeps = 1 if args.lse_fed else 2
+    sweeps, kernel = saliency_form(R, args.lse_fed, args.schedule)
     lh_sal = (n_sh * Hkv) if shared else lh
     k_bytes = lh_sal * ntot * d * 2
     sal_flops = sweeps * 2 * R * d * ntot * lh_sal     # Q K^T once per sweep
@@ -593,8 +604,6 @@ def main():
     t_cmp = stage_ms["compact"] * 1e-3
     achieved_tflops = sal_flops / t_sal / 1e12
     achieved_gbs = sal_bytes / t_sal / 1e9
-    kernel = ("saliency (one MFMA sweep over K, row LSE given)" if args.lse_fed
-              else "saliency (two MFMA sweeps over K)")
     if shared:
         kernel = f"shared-index scoring: {kernel} of the last {n_sh} layers, head sum, priority"
     traffic = recorded_traffic(traffic_key(args.workload, budget, w.window, args.lse_fed,

@@ -43,3 +43,12 @@ def test_traffic_records_follow_every_source_of_the_sweeps(tmp_path, monkeypatch
         assert bench.source_digest() != start, name
         (dst / name).write_bytes(text)
     assert bench.source_digest() == start
+
+
+def test_saliency_form_counts_the_passes_over_k():
+    assert bench.saliency_form(256, False, 0)[0] == 2
+    assert bench.saliency_form(256, True, 0)[0] == 1
+    # at most 8 window rows keep their logits, unless a schedule is forced
+    assert bench.saliency_form(4, False, 0)[0] == bench.saliency_form(8, False, 0)[0] == 1
+    assert bench.saliency_form(9, False, 0)[0] == 2
+    assert bench.saliency_form(4, False, 1)[0] == bench.saliency_form(4, False, 2)[0] == 2
