@@ -442,15 +442,16 @@ void decode_mfma_kernel(DecodeArgs a) {
 
 // out[l][s][hq] = merge of the splits of sequence s (o / z; zero rows give 0),
 // for the G query heads of a KV head (HEADS_G) or for one of them per workgroup:
-//   M and Z per head: a lane per split; the weights 2^(m - M) of up to
-//   kBlockSplits splits at a time go to LDS;
+//   M and Z per head: a lane per split, which puts its split's weight 2^(m - M)
+//   into LDS (kBlockSplits at a time);
 //   O: a thread per (head, dim) adds the splits' weighted partial outputs, in
 //   order; with one head per workgroup THREADS / D groups of threads share the
 //   splits and their sums are added in group order.
 // The first splits' partial outputs are loaded before the weights are known, so
 // that a merge of few splits waits for memory once. The chain of loads bounds
 // it: 8 heads x 30000 rows (59 splits) took 43.8 us a step with a thread per dim
-// and eight splits at a time, now 29.1.
+// and eight splits at a time, now 29.1; 8 heads x 300 rows 10.6, 10.3 with a
+// second load of m for the weights, now 9.95 (d 64, G 4).
 constexpr int kBlockSplits = 64;
 
 template <int D, int THREADS, bool HEADS_G>
@@ -460,7 +461,7 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
   constexpr int kHeads = HEADS_G ? 16 : 1;
   constexpr int J = HEADS_G ? 1 : THREADS / D;  // thread groups over the splits
   constexpr int kAhead = 4;                     // partial outputs loaded ahead per thread
-  static_assert(THREADS % D == 0, "whole groups");
+  static_assert(THREADS % D == 0 && kBlockSplits == kWave, "whole groups, a split per lane");
   __shared__ float wts[kHeads][kBlockSplits];
   __shared__ float zsum[kHeads], mref[kHeads];
   __shared__ float osum[J][D];
@@ -496,16 +497,21 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
     const int j = jg + J * u;
     ahead[u] = j < n && e0 < nh * D ? base[j * stride + (e0 / D) * ST + e0 % D] : 0.f;
   }
-  // M and Z of every head
+  // M, Z and the first splits' weights of every head, from one load per lane
   for (int g = wave; g < nh; g += kWavesC) {
     const float* __restrict__ p = base + (size_t)g * ST + D;
-    float m = -INFINITY;
-    for (int j = lane; j < n; j += kWave) m = fmaxf(m, p[j * stride]);
+    const float m0 = lane < n ? p[lane * stride] : -INFINITY;
+    const float z0 = lane < n ? p[lane * stride + 1] : 0.f;
+    float m = m0;
+    for (int j = lane + kWave; j < n; j += kWave) m = fmaxf(m, p[j * stride]);
     m = wave_max(m);
-    float z = 0.f;
+    const float w0 = m == -INFINITY ? 0.f : fast_exp2(m0 - m);
+    float z = m == -INFINITY ? 0.f : z0 * w0;
     if (m != -INFINITY)
-      for (int j = lane; j < n; j += kWave) z += p[j * stride + 1] * fast_exp2(p[j * stride] - m);
+      for (int j = lane + kWave; j < n; j += kWave)
+        z += p[j * stride + 1] * fast_exp2(p[j * stride] - m);
     z = wave_sum(z);
+    wts[g][lane] = w0;
     if (lane == 0) {
       mref[g] = m;
       zsum[g] = z;
@@ -516,14 +522,6 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
     const float m = mref[g];
     return m == -INFINITY ? 0.f : fast_exp2(base[j * stride + (size_t)g * ST + D] - m);
   };
-  auto weights = [&](int j0) {  // of splits j0 .. j0 + kBlockSplits - 1
-    for (int e = tid; e < nh * kBlockSplits; e += THREADS) {
-      const int g = e / kBlockSplits, j = e % kBlockSplits;
-      if (j0 + j < n) wts[g][j] = weight(g, j0 + j);
-    }
-  };
-  weights(0);
-  __syncthreads();
   float* __restrict__ out = a.out + (((size_t)l * a.S + s) * a.Hq + h * a.G + g0) * D;
   if constexpr (HEADS_G) {
     for (int e = e0; e < nh * D; e += THREADS) {
@@ -548,7 +546,7 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(DecodeArgs a) {
     for (int j0 = 0; j0 < n; j0 += kBlockSplits) {
       if (j0 > 0) {
         __syncthreads();
-        weights(j0);
+        if (tid < kBlockSplits && j0 + tid < n) wts[0][tid] = weight(0, j0 + tid);
         __syncthreads();
       }
       const int end = min(n - j0, kBlockSplits);
@@ -617,10 +615,11 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
     // With at most one workgroup per CU, more waves share each split (8 at d
     // 128, 16 at d 64, as the registers allow), so that a wave walks fewer
     // tiles: one layer of 8 heads x 1536 rows 13.9 -> 13.1 us, of 300 rows
-    // 12.4 -> 11.4; with 320 workgroups of 4 waves 27.0, of 8 waves 30.3.
+    // 12.4 -> 11.4; with 320 workgroups of 4 waves 27.0, of 8 waves 30.3. 16 waves
+    // lose 0.2 to 0.4 us on sequences of 33 rows or fewer.
     auto split = [&](auto d_c) {
       constexpr int D = decltype(d_c)::value;
-      if (grid.x <= 256)
+      if (grid.x <= 256 && (D == 128 || a.out_rows >= 64 * (int64_t)a.S))
         hipLaunchKernelGGL((decode_mfma_kernel<D, 1024 / D>), grid, dim3(1024 / D * kWave), 0, st, a);
       else
         hipLaunchKernelGGL((decode_mfma_kernel<D, 4>), grid, dim3(kThreads), 0, st, a);
@@ -629,21 +628,28 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
     else split(std::integral_constant<int, 64>{});
   }
   // All heads of a KV head per workgroup when those fill the chip (28 layers x 4
-  // heads x 16 sequences: the step 419 -> 411 us; one head each: 448); otherwise
-  // one head each, with several groups of threads over the splits while the
-  // workgroups are few (256 KV heads x 300 rows: 15.3 us with 128 threads, 16.9
-  // with 512).
+  // heads x 16 sequences, G 7: the step 419 -> 411 us; one head each: 448), or with
+  // few splits to add where the threads hold every (head, dim) once (one layer of 8
+  // heads x 28 sequences x 512 rows, d 64, G 4: 13.5 us; one head each 14.1, with
+  // several groups of threads 15.5). Otherwise one head each, with several groups of
+  // threads over many splits while the workgroups are few (8 heads x 9000 rows:
+  // 17.3 us, with 128 threads 18.7, all heads 21.4).
   auto combine = [&](auto d_c) {
     constexpr int D = decltype(d_c)::value;
     const unsigned kv = (unsigned)(a.L * a.S * a.Hkv);
-    if (kv >= 512)
-      hipLaunchKernelGGL((decode_combine_kernel<D, 256, true>), dim3(kv), dim3(256), 0, st, a);
-    else if (kv * (unsigned)a.G >= 1024)
+    const bool few = a.total_splits <= 4 * (int64_t)a.S;
+    if (kv >= 512 ? a.G > 1 : few && a.G * D <= 256) {
+      if (a.G * D <= 128)
+        hipLaunchKernelGGL((decode_combine_kernel<D, 128, true>), dim3(kv), dim3(128), 0, st, a);
+      else
+        hipLaunchKernelGGL((decode_combine_kernel<D, 256, true>), dim3(kv), dim3(256), 0, st, a);
+    } else if (kv >= 512 || few || kv * (unsigned)a.G >= 1024) {
       hipLaunchKernelGGL((decode_combine_kernel<D, 128, false>), dim3(kv * (unsigned)a.G),
                          dim3(128), 0, st, a);
-    else
+    } else {
       hipLaunchKernelGGL((decode_combine_kernel<D, 512, false>), dim3(kv * (unsigned)a.G),
                          dim3(512), 0, st, a);
+    }
   };
   if (a.d == 128) combine(std::integral_constant<int, 128>{});
   else combine(std::integral_constant<int, 64>{});

@@ -1,7 +1,7 @@
-"""Decode: splits shared by 4, 8 and 16 waves and the three forms of the merge (all heads of a
-KV head per workgroup; one head with one or several thread groups over the splits), each with
-one split, a few and more than 64 per sequence, empty and one-row sequences and an out_rows that
-cuts the last one.
+"""Decode: splits shared by 4, 8 and 16 waves and the four forms of the merge (all heads of a
+KV head per workgroup of 128 or 256 threads; one head with one or several thread groups over the
+splits), each with one split, a few and more than 64 per sequence, empty and one-row sequences, an
+out_rows that cuts the last one, and NaN and infinite rows.
 P enters the second product as two bf16 parts (2^-17 relative) and every sum is fp32, so an
 output differs from float64 attention by less than 2^-15 of its row's largest magnitude."""
 import numpy as np
@@ -26,6 +26,15 @@ CASES = {
     # fewer, but 1024 query heads: 128 threads per head; 1, 6 and 79 splits
     "one_head_128_splits": (1, 8, 1, 64, [3000, 40000, 1] + [0, 20] * 70, 0),
     "one_head_128_splits_d128": (2, 64, 4, 128, [2700, 33300] + [0, 9] * 10, 5),
+    # at least 64 rows a sequence on average: 16 waves at d 64
+    "waves16_edges_64_rows": (1, 8, 2, 64, [63, 64, 65, 0, 1, 127, 200], 1),
+    # few splits a sequence on average, (head, dim) pairs for 256 or 128 threads
+    "few_all_heads_256": (1, 8, 2, 64, [33300, 700] + [0, 5, 513] * 20, 3),
+    "few_all_heads_128": (1, 2, 2, 64, [3, 40000, 2600] + [0, 1, 17] * 30, 0),
+    "few_all_heads_128_d128": (4, 8, 8, 128, [512, 1], 0),
+    # kv heads x sequences >= 512: 128 threads for two heads of d 64, one head each of G 1
+    "all_heads_128_splits": (2, 8, 4, 64, [40000, 2600] + [0, 1, 17] * 30, 0),
+    "one_of_one_head": (1, 4, 4, 128, [33300, 2600] + [0, 5, 600] * 50, 2),
 }
 
 
@@ -62,3 +71,43 @@ def test_decode_merge(case):
         ref = (torch.softmax(z, -1)[..., None] * vv).sum(2)
         err = (out[:, s] - ref).abs().amax(-1) / ref.abs().amax(-1)
         assert float(err.max()) < 2.0 ** -15
+
+
+@pytest.mark.parametrize("case", ["waves8", "waves16_edges_64_rows", "waves4_many_splits",
+                                  "one_head_128", "few_all_heads_256", "few_all_heads_128",
+                                  "all_heads", "all_heads_128_splits"])
+def test_non_finite_rows_stay_in_their_sequence(case):
+    """A sequence whose keys hold a NaN and infinities leaves every other sequence bit for bit as
+    it was; a NaN and an infinity in V reach their own (head, dim) columns alone."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    L, Hq, Hkv, d, rows, _ = CASES[case]
+    G = Hq // Hkv
+    cu = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    n = int(cu[-1])
+    pb = B.Problem(L, Hq, Hkv, d, 1, cu, np.zeros(len(rows) + 1, np.int32))
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q = torch.randn((L, len(rows), Hq, d), generator=gen, device="cuda").to(torch.bfloat16)
+    k, v = (torch.randn((L, Hkv, n, d), generator=gen, device="cuda").to(torch.bfloat16)
+            for _ in range(2))
+    cud = torch.from_numpy(cu).cuda()
+    log(f"[decode merge non-finite {case}]")
+    good = B.decode_attention(pb, q, k, v, cud, n)
+    s = int(np.argmax(rows))
+    a, b = int(cu[s]), int(cu[s + 1])
+    bad_k = k.clone()
+    bad_k[0, 0, a, 0], bad_k[0, 0, b - 1, 1] = float("inf"), float("nan")
+    bad_k[0, 0, (a + b) // 2, 2] = float("-inf")
+    out = B.decode_attention(pb, q, bad_k, v, cud, n)
+    other = torch.ones_like(good, dtype=torch.bool)
+    other[0, s, :G] = False
+    assert torch.equal(out[other], good[other])
+    bad_v = v.clone()
+    bad_v[0, 0, a, 0], bad_v[0, 0, b - 1, 5] = float("nan"), float("inf")
+    out = B.decode_attention(pb, q, k, bad_v, cud, n)
+    other = torch.ones_like(good, dtype=torch.bool)
+    other[0, s, :G, 0] = other[0, s, :G, 5] = False
+    assert torch.equal(out[other], good[other])
+    assert bool(torch.isnan(out[0, s, :G, 0]).all()) and not bool(out[0, s, :G, 5].isfinite().any())
