@@ -698,9 +698,13 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectArgs a) {
 // selection before (separate launches) and now: 256 rows of 32768 tokens
 // 33 + 25 -> 27 us, of 16384 22 + 24 -> 19, 8 rows of 8192 10 + 21 -> 10, 2 rows
 // of 1024 9.5 + 20 -> 7.7, 16 sequences of 4k to 32k tokens x 112 heads
-// 98 + 206 -> 152. Rows of up to 8 blocks (more do not fit the registers),
-// pooling windows of up to 9 and up to kRankSteps steps per sequence (the table
-// of step utilities in LDS).
+// 98 + 206 -> 152. Rows of up to 8 blocks, pooling windows of up to 9 and up to
+// kRankSteps steps per sequence (the table of step utilities in LDS). 1024
+// threads leave each 128 VGPRs: code for 8 blocks takes 113 to 121 of them up to
+// windows of 5, all and 4 more in scratch at 7, and 21 to 26 in scratch at 9, all
+// with about 20 scalars kept in vector lanes; code for 4 blocks takes 54 to 80
+// (72 at a window of 7, so that one workgroup is resident on a CU, not two).
+// Rows of 16 blocks would spill most of theirs.
 constexpr int kRankSteps = 4096;
 constexpr int kRankHalf = 4;
 constexpr int kRankBlocks = 8;
@@ -905,8 +909,10 @@ hipError_t launch_rank(const FuseArgs& f, const SelectArgs& a, hipStream_t st) {
 }
 
 // The least kernel that holds the longest row: code for more blocks takes more
-// registers (84 for 8 blocks against 46 for up to 4, which lets two workgroups
-// share a CU). Past 16 blocks the keys do not fit the register file.
+// registers (82 for 8 blocks against 45 for up to 4, which lets two workgroups
+// share a CU). With 16 blocks the 64 keys of a thread and the rest exceed its 128
+// VGPRs: 58 are spilled to scratch, and it is still faster than reading the row
+// again (8 rows of 60000, budget 2048: 26 us, streamed 36). Past 16 blocks they cannot be held.
 hipError_t launch_select(const SelectArgs& a, hipStream_t st) {
   if (a.S * a.LH == 0) {
     hipLaunchKernelGGL(retained_plan_kernel, dim3(1), dim3(kThreads), 0, st, a);
