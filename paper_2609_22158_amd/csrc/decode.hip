@@ -402,7 +402,8 @@ void decode_mfma_kernel(DecodeArgs a) {
 #pragma unroll
         for (int v = 0; v < NW; ++v) Z += wstate[v][g][D + 1] * fast_exp2(wstate[v][g][D] - M);
       }
-      fscale[w][g] = M == -INFINITY ? 0.f : fast_exp2(wstate[w][g][D] - M);
+      // -1: no logit but NaN, and the split adds nothing, as with 4 waves
+      fscale[w][g] = M == -INFINITY ? -1.f : fast_exp2(wstate[w][g][D] - M);
       if (w == 0) {
         part0[g * ST + D] = M;
         part0[g * ST + D + 1] = Z;
@@ -414,7 +415,7 @@ void decode_mfma_kernel(DecodeArgs a) {
       float O = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) O = fmaf(wstate[w][g][dd], fscale[w][g], O);
-      part0[g * ST + dd] = O;
+      part0[g * ST + dd] = fscale[0][g] < 0.f ? 0.f : O;
     }
     return;
   }

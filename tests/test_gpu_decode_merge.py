@@ -111,3 +111,28 @@ def test_non_finite_rows_stay_in_their_sequence(case):
     other[0, s, :G, 0] = other[0, s, :G, 5] = False
     assert torch.equal(out[other], good[other])
     assert bool(torch.isnan(out[0, s, :G, 0]).all()) and not bool(out[0, s, :G, 5].isfinite().any())
+
+
+@pytest.mark.parametrize("L,d", [(1, 64), (1, 128), (80, 64), (80, 128)])
+def test_split_of_nan_alone_adds_nothing(L, d):
+    """The last key, alone in its split, is NaN: the output is the attention over the other rows,
+    with a few workgroups of 8 or 16 waves as with many of 4."""
+    import torch
+
+    from paper_2609_22158_amd import binding as B
+
+    n, H, G = 1025, 2, 4
+    cu = np.array([0, n], np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    q = torch.randn((L, 1, H * G, d), generator=gen, device="cuda").to(torch.bfloat16)
+    k, v = (torch.randn((L, H, n, d), generator=gen, device="cuda").to(torch.bfloat16)
+            for _ in range(2))
+    k[:, :, n - 1] = float("nan")
+    log(f"[decode NaN split L={L} d={d}]")
+    out = []
+    for rows in (n, n - 1):
+        pb = B.Problem(L, H * G, H, d, 1, np.array([0, rows]), np.zeros(2, np.int32))
+        out.append(B.decode_attention(pb, q, k[:, :, :rows].contiguous(), v[:, :, :rows].contiguous(),
+                                      torch.from_numpy(cu).cuda().clamp(max=rows), rows))
+    # the same partial states but for the merge's forms, which add in another order
+    torch.testing.assert_close(out[0], out[1], rtol=1e-5, atol=1e-6)
